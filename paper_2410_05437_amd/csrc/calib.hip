@@ -380,7 +380,8 @@ int autocorr_ranges(int64_t M, int64_t K, bool f32) {
 }
 
 hipError_t launch_autocorr_update(const void* X, int64_t ldx, int M, int K, bool f32, bool normalize,
-                                  float alpha, float* C, int64_t ldc, void* workspace, hipStream_t stream) {
+                                  float alpha, float* C, int64_t ldc, void* workspace, int cus,
+                                  hipStream_t stream) {
     const int64_t ldt = (M + 7) / 8 * 8;
     unsigned char* ws = static_cast<unsigned char*>(workspace);
     size_t off = (size_t)K * ldt * (f32 ? 4 : 2);
@@ -415,7 +416,7 @@ hipError_t launch_autocorr_update(const void* X, int64_t ldx, int M, int K, bool
 
     if (f32) {
         const float* Xt = reinterpret_cast<const float*>(ws);
-        e = launch_gemm_tn_f32(Xt, ldt, Xt, ldt, part, ldp, K, K, M, stream);
+        e = launch_gemm_tn_f32(Xt, ldt, Xt, ldt, part, ldp, K, K, M, cus, stream);
     } else {
         GemmArgs g{};
         g.A = reinterpret_cast<const uint16_t*>(ws);
@@ -461,11 +462,11 @@ size_t pca_workspace_bytes(int64_t K) {
 size_t symprod_workspace_bytes(int64_t K) { return (size_t)K * splitk_ld((int)K) * 4; }
 
 hipError_t launch_symmetrized_product(const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
-                                      int64_t ldc, int K, float alpha, float beta, void* workspace,
+                                      int64_t ldc, int K, float alpha, float beta, void* workspace, int cus,
                                       hipStream_t stream) {
     float* P = static_cast<float*>(workspace);
     const int64_t ldp = splitk_ld(K);
-    hipError_t e = launch_gemm_tn_f32(A, lda, B, ldb, P, ldp, K, K, K, stream);
+    hipError_t e = launch_gemm_tn_f32(A, lda, B, ldb, P, ldp, K, K, K, cus, stream);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(symmetrize_kernel, dim3(ceil_div_i(K, 64), ceil_div_i(K, 64)), dim3(256), 0, stream, P,
                        ldp, C, ldc, K, alpha, beta);

@@ -562,7 +562,7 @@ espace_status run_tn(const void* A, int64_t lda, const void* B, int64_t ldb, voi
     hipError_t e;
     if (dt == ESPACE_F32) {
         e = espace::launch_gemm_tn_f32((const float*)A, lda, (const float*)B, ldb, (float*)C, ldc,
-                                       (int)R, (int)Cc, (int)D, stream);
+                                       (int)R, (int)Cc, (int)D, device_cus(), stream);
     } else {
         const Plan p = plan_tn_logged(R, Cc, D, dt);
         GemmArgs g;
@@ -1048,7 +1048,7 @@ espace_status espace_autocorrelation_update(const void* X, int64_t ldx, float* C
     ESPACE_TRY(check_alias(mat_range("C", C, K, ldc, ESPACE_F32), ins, 2));
     ESPACE_TRY(check_device());
     const hipError_t e = espace::launch_autocorr_update(X, ldx, (int)N, (int)K, dt == ESPACE_F32, normalize != 0,
-                                                        alpha, C, ldc, workspace, stream);
+                                                        alpha, C, ldc, workspace, device_cus(), stream);
     if (e != hipSuccess) return fail(ESPACE_ERR_HIP, "autocorrelation update: %s", hipGetErrorString(e));
     return ok();
 }
@@ -1067,8 +1067,8 @@ espace_status espace_symmetrized_product(const float* A, int64_t lda, const floa
                          Range{"workspace", (uintptr_t)workspace, (uintptr_t)workspace + workspace_bytes}};
     ESPACE_TRY(check_alias(mat_range("C", C, K, ldc, ESPACE_F32), ins, 3));
     ESPACE_TRY(check_device());
-    const hipError_t e =
-        espace::launch_symmetrized_product(A, lda, B, ldb, C, ldc, (int)K, alpha, beta, workspace, stream);
+    const hipError_t e = espace::launch_symmetrized_product(A, lda, B, ldb, C, ldc, (int)K, alpha, beta, workspace,
+                                                            device_cus(), stream);
     if (e != hipSuccess) return fail(ESPACE_ERR_HIP, "symmetrized product: %s", hipGetErrorString(e));
     return ok();
 }

@@ -1,19 +1,18 @@
-// float32 "TN" product C[r][c] = sum_k A[r][k] * B[c][k] with fp32 FMA.
+// float32 "TN" product C[r][c] = sum_k A[r][k] * B[c][k] on the fp32 MFMA
+// (the float32 layers and gradients, the calibration products).
 //
-// The fp32 layer variant is small (it serves the float32 workloads and the
-// exactness checks); a 64x64 tile per 256-thread workgroup, 16-deep LDS
-// steps, 4x4 outputs per thread.  Tiles are stored k-major in LDS so each
-// thread reads its four rows / four columns as one 16-byte vector.
+// fp32 MFMA issue 256 flops per clock and CU, twice the vector ALU's rate
+// without packed instructions.  In both kernels the MFMA takes the B rows as
+// its first operand, so a lane ends with runs of 4 consecutive output columns
+// of one row, and the depth index of an operand is permuted the same way for
+// both: a lane's 16-byte chunk holds 4 consecutive k, chunk q of a row goes
+// to lane group q, and MFMA e of a slab takes element e of every chunk.
 #include "common.hpp"
 #include "kernels.hpp"
 
 namespace espace {
 
 namespace {
-
-constexpr int FT = 64;    // tile edge
-constexpr int FK = 16;    // depth step
-constexpr int FPAD = 4;
 
 __device__ __forceinline__ f32x4_t load4_masked(const float* row, int k, int depth) {
     f32x4_t v = {0.f, 0.f, 0.f, 0.f};
@@ -28,72 +27,231 @@ __device__ __forceinline__ f32x4_t load4_masked(const float* row, int k, int dep
     return v;
 }
 
-__global__ __launch_bounds__(256)
-void gemm_tn_f32_kernel(const float* __restrict__ A, int64_t lda,
-                        const float* __restrict__ B, int64_t ldb,
-                        float* __restrict__ C, int64_t ldc, int R, int Cc, int D) {
-    __shared__ float As[FK][FT + FPAD];
-    __shared__ float Bs[FK][FT + FPAD];
-    const int tid = threadIdx.x;
-    const int tx = tid & 15;
-    const int ty = tid >> 4;
-    const int row0 = blockIdx.y * FT;
-    const int col0 = blockIdx.x * FT;
-    // loader: row tid/4, 4 consecutive k at (tid%4)*4
-    const int lr = tid >> 2;
-    const int lk = (tid & 3) * 4;
-    int ar = row0 + lr;
-    ar = ar < R ? ar : R - 1;
-    int bc = col0 + lr;
-    bc = bc < Cc ? bc : Cc - 1;
-    const float* arow = A + (int64_t)ar * lda;
-    const float* brow = B + (int64_t)bc * ldb;
+template <int MI> struct AccF;
+template <> struct AccF<32> { typedef f32x16_t type; };
+template <> struct AccF<16> { typedef f32x4_t type; };
 
-    float acc[4][4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) acc[i][j] = 0.f;
+__device__ __forceinline__ f32x16_t mfma_f32(float b, float a, f32x16_t c) {
+    return __builtin_amdgcn_mfma_f32_32x32x2f32(b, a, c, 0, 0, 0);
+}
+__device__ __forceinline__ f32x4_t mfma_f32(float b, float a, f32x4_t c) {
+    return __builtin_amdgcn_mfma_f32_16x16x4f32(b, a, c, 0, 0, 0);
+}
 
-    for (int k0 = 0; k0 < D; k0 += FK) {
-        const f32x4_t va = load4_masked(arow, k0 + lk, D);
-        const f32x4_t vb = load4_masked(brow, k0 + lk, D);
+// Four consecutive columns c .. c + 3 of output row `row`.
+__device__ __forceinline__ void store4(float* row, int c, int Cc, f32x4_t v) {
+    if (c + 4 <= Cc) {
+        *reinterpret_cast<f32x4_t*>(row + c) = v;
+    } else {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-            As[lk + e][lr] = va[e];
-            Bs[lk + e][lr] = vb[e];
+        for (int e = 0; e < 4; ++e)
+            if (c + e < Cc) row[c + e] = v[e];
+    }
+}
+
+// Tiles of BM x BN outputs, four waves as 2 x 2, each a grid of 32 x 32 blocks
+// of v_mfma_f32_32x32x2_f32.  Bound by the matrix cores: a 32-deep step of a
+// 128 x 128 tile is 4096 cycles of MFMA per SIMD against 32 KB of operands, so
+// two LDS stages of 128-byte rows, two workgroups per CU and one barrier per
+// step suffice: 4096^3 in 1030 us, 133 TFLOP/s of the 157 the matrix cores
+// issue (the vector-ALU kernel before it, 64 x 64 tiles: 1760 us; 1100 x 2048
+// x 2048: 172 -> 103 us; 1024^3: 65 -> 24 us).  Chunk c of row r sits at chunk c ^ ((r >> 1) & 7): the 16 rows
+// that 16 neighbouring lanes read fall on all 64 banks.
+constexpr int TK = 32;                            // depth step: 128-byte rows
+
+template <int BM, int BN>
+__global__ __launch_bounds__(256, 2)
+void gemm_tn_f32_mfma_kernel(const float* __restrict__ A, int64_t lda, const float* __restrict__ B, int64_t ldb,
+                             float* __restrict__ C, int64_t ldc, int R, int Cc, int D, int tiles_c) {
+    constexpr int WM = BM / 2, WN = BN / 2, TM = WM / 32, TN = WN / 32;
+    constexpr int STAGE = (BM + BN) * TK * 4;
+    constexpr int LPW = (BM + BN) / 8 / 4;        // 1 KB loads (8 rows) per wave and stage
+    __shared__ __attribute__((aligned(1024))) unsigned char smem[2 * STAGE];
+    int tile_r, tile_c;
+    tile_coords<4>(blockIdx.x, gridDim.x, tiles_c, 0, tile_r, tile_c);
+    const int row0 = tile_r * BM, col0 = tile_c * BN;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int wr0 = (wave >> 1) * WM, wc0 = (wave & 1) * WN;
+
+    // descriptors over the tile's own rows (the launcher checks that these
+    // span less than 2^32 bytes); rows past the matrix repeat its last row
+    const int nr = min(BM, R - row0), nc = min(BN, Cc - col0);
+    const auto ra = __builtin_amdgcn_make_buffer_rsrc((void*)(A + (int64_t)row0 * lda), (short)0,
+                                                      (int)(uint32_t)((uint64_t)nr * lda * 4u), 0x00020000);
+    const auto rb = __builtin_amdgcn_make_buffer_rsrc((void*)(B + (int64_t)col0 * ldb), (short)0,
+                                                      (int)(uint32_t)((uint64_t)nc * ldb * 4u), 0x00020000);
+    unsigned off[LPW];
+    int kc[LPW];
+#pragma unroll
+    for (int j = 0; j < LPW; ++j) {
+        const int q = wave + 4 * j;
+        const int rl = 8 * q + (lane >> 3);
+        const bool isA = 8 * q < BM;
+        const int rr = isA ? rl : rl - BM;
+        kc[j] = ((lane & 7) ^ ((rr >> 1) & 7)) * 4;
+        const int g = isA ? min(rr, nr - 1) : min(rr, nc - 1);
+        off[j] = (unsigned)(((uint64_t)g * (isA ? lda : ldb) + kc[j]) * 4u);
+    }
+    auto issue = [&](int t) {
+        unsigned char* stage = smem + (t & 1) * STAGE;
+        const int k0 = t * TK;
+#pragma unroll
+        for (int j = 0; j < LPW; ++j) {
+            const int q = wave + 4 * j;
+            // chunks at or past the depth are read past the descriptor: zeros
+            const unsigned o = k0 + kc[j] < D ? off[j] + (unsigned)k0 * 4u : 0xFFFFFFF0u;
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(8 * q < BM ? ra : rb,
+                                                     (__attribute__((address_space(3))) void*)(stage + q * 1024), 16,
+                                                     (int)o, 0, 0, 0);
         }
-        __syncthreads();
+    };
+
+    f32x16_t acc[TM][TN];
 #pragma unroll
-        for (int kk = 0; kk < FK; ++kk) {
-            const f32x4_t a = *reinterpret_cast<const f32x4_t*>(&As[kk][ty * 4]);
-            const f32x4_t b = *reinterpret_cast<const f32x4_t*>(&Bs[kk][tx * 4]);
+    for (int i = 0; i < TM; ++i)
 #pragma unroll
-            for (int i = 0; i < 4; ++i)
+        for (int j = 0; j < TN; ++j)
 #pragma unroll
-                for (int j = 0; j < 4; ++j) acc[i][j] = __builtin_fmaf(a[i], b[j], acc[i][j]);
+            for (int e = 0; e < 16; ++e) acc[i][j][e] = 0.f;
+
+    const int lr = lane & 31, lh = lane >> 5, sw = (lr >> 1) & 7;
+    const int steps = (D + TK - 1) / TK;
+    issue(0);
+    for (int t = 0; t < steps; ++t) {
+        // this wave's loads of step t have landed, and after the barrier
+        // every wave's; every wave is done reading the other stage
+        asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+        if (t + 1 < steps) issue(t + 1);
+        const unsigned char* stage = smem + (t & 1) * STAGE;
+        const unsigned char* pa = stage + (wr0 + lr) * (TK * 4);
+        const unsigned char* pb = stage + (BM + wc0 + lr) * (TK * 4);
+        const int left = D - t * TK;              // only the last step has fewer than TK
+#pragma unroll
+        for (int s = 0; s < TK / 8; ++s) {
+            const int c = ((2 * s + lh) ^ sw) * 16;
+            f32x4_t fa[TM], fb[TN];
+#pragma unroll
+            for (int i = 0; i < TM; ++i) fa[i] = *reinterpret_cast<const f32x4_t*>(pa + i * 32 * TK * 4 + c);
+#pragma unroll
+            for (int j = 0; j < TN; ++j) fb[j] = *reinterpret_cast<const f32x4_t*>(pb + j * 32 * TK * 4 + c);
+            if (left < TK) {
+                // the chunk that straddles the depth: its padding is not used
+                const int nv = left - 8 * s - 4 * lh;
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+#pragma unroll
+                    for (int i = 0; i < TM; ++i) fa[i][e] = e < nv ? fa[i][e] : 0.f;
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) fb[j][e] = e < nv ? fb[j][e] : 0.f;
+                }
+            }
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int i = 0; i < TM; ++i)
+#pragma unroll
+                    for (int j = 0; j < TN; ++j) acc[i][j] = mfma_f32(fb[j][e], fa[i][e], acc[i][j]);
         }
-        __syncthreads();
     }
 #pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const int r = row0 + ty * 4 + i;
+    for (int i = 0; i < TM; ++i) {
+        const int r = row0 + wr0 + 32 * i + lr;
         if (r >= R) continue;
+        float* row = C + (int64_t)r * ldc;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            const int c = col0 + tx * 4 + j;
-            if (c < Cc) C[(int64_t)r * ldc + c] = acc[i][j];
-        }
+        for (int j = 0; j < TN; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+                store4(row, col0 + wc0 + 32 * j + 8 * q + 4 * lh, Cc,
+                       f32x4_t{acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]});
     }
+}
+
+// Products too small to fill the chip with tiles: one MI x MI block of the
+// output per workgroup, its W waves taking turns at the depth (UD consecutive
+// slabs of 256 / MI each, loaded straight to registers), the partial sums
+// added in wave order through LDS.  Bound by latency, or by the stream of the
+// many-row operand for a few tokens: with the depth one serial chain per tile
+// the 128 x 64 x 256 projection took 17 us and 16 x 4096 x 2048 130 us, now
+// below 10 us with the launch.
+template <int MI, int W, int UD>
+__global__ __launch_bounds__(W * 64)
+void gemm_tn_f32_split_kernel(const float* __restrict__ A, int64_t lda, const float* __restrict__ B, int64_t ldb,
+                              float* __restrict__ C, int64_t ldc, int R, int Cc, int D, int tiles_c) {
+    using Acc = typename AccF<MI>::type;
+    constexpr int SD = 256 / MI;                  // depth of a slab: one 16-byte chunk per lane
+    constexpr int NQ = MI * MI / 256;             // 4-column runs per lane
+    __shared__ f32x4_t red[W][NQ][64];
+    int tile_r, tile_c;
+    tile_coords<4>(blockIdx.x, gridDim.x, tiles_c, 0, tile_r, tile_c);
+    const int row0 = tile_r * MI, col0 = tile_c * MI;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int lr = lane % MI, lk = lane / MI * 4;
+    const float* arow = A + (int64_t)min(row0 + lr, R - 1) * lda;
+    const float* brow = B + (int64_t)min(col0 + lr, Cc - 1) * ldb;
+    Acc acc;
+#pragma unroll
+    for (int e = 0; e < 4 * NQ; ++e) acc[e] = 0.f;
+    for (int k0 = wave * UD * SD; k0 < D; k0 += W * UD * SD) {
+        f32x4_t fa[UD], fb[UD];
+        if (k0 + UD * SD <= D) {
+#pragma unroll
+            for (int u = 0; u < UD; ++u) {
+                fb[u] = *reinterpret_cast<const f32x4_t*>(brow + k0 + u * SD + lk);
+                fa[u] = *reinterpret_cast<const f32x4_t*>(arow + k0 + u * SD + lk);
+            }
+        } else {
+#pragma unroll
+            for (int u = 0; u < UD; ++u) {
+                fb[u] = load4_masked(brow, k0 + u * SD + lk, D);
+                fa[u] = load4_masked(arow, k0 + u * SD + lk, D);
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < UD; ++u)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) acc = mfma_f32(fb[u][e], fa[u][e], acc);
+    }
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) red[wave][q][lane] = f32x4_t{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
+    __syncthreads();
+    if (wave >= NQ) return;
+    f32x4_t v = red[0][wave][lane];
+#pragma unroll
+    for (int w = 1; w < W; ++w) v += red[w][wave][lane];
+    const int r = row0 + lr;
+    if (r < R) store4(C + (int64_t)r * ldc, col0 + 8 * wave + lk, Cc, v);
 }
 
 }  // namespace
 
+
 hipError_t launch_gemm_tn_f32(const float* A, int64_t lda, const float* B, int64_t ldb,
-                              float* C, int64_t ldc, int R, int Cc, int D, hipStream_t stream) {
-    dim3 grid((Cc + FT - 1) / FT, (R + FT - 1) / FT);
-    hipLaunchKernelGGL(gemm_tn_f32_kernel, grid, dim3(256), 0, stream, A, lda, B, ldb, C, ldc,
-                       R, Cc, D);
+                              float* C, int64_t ldc, int R, int Cc, int D, int cus, hipStream_t stream) {
+    auto tiles = [&](int t) { return (int64_t)((R + t - 1) / t) * ((Cc + t - 1) / t); };
+    // the tiled kernels' 32-bit offsets inside a tile
+    const bool fits = (lda > ldb ? lda : ldb) * 128 * 4 < ((int64_t)1 << 32);
+#define LAUNCH(KERNEL, TILE, THREADS)                                                                          \
+    hipLaunchKernelGGL(KERNEL, dim3((unsigned)tiles(TILE)), dim3(THREADS), 0, stream, A, lda, B, ldb, C, ldc, R, \
+                       Cc, D, (Cc + TILE - 1) / TILE)
+    // 128 x 128 tiles once there is one for every CU (4096^3, 1024 tiles:
+    // 1030 against 1079 us with 64 x 64 tiles; 2048 x 2048 x 8192, 256: 542
+    // against 549; 1100 x 2048 x 2048, 153: 132 against 103); 64 x 64 tiles
+    // from half as many as CUs (1000 x 600 x 1500, 160 tiles: 33 against 36
+    // us with 32 x 32 blocks; 200 x 1024 x 1024, 64: 23 against 11).  Below
+    // that the depth is split over a workgroup's waves: 32 x 32 blocks from
+    // 5/8 as many as CUs (200 x 1024 x 1024, 224 blocks: 11 against 17 us
+    // with 16 x 16 ones; 200 x 300 x 2000, 70: 16 against 9.5), 16 x 16
+    // blocks below, and always up to 16 rows, where half of a 32-row block
+    // would be empty (16 x 4096 x 2048: 9.7 against 16 us).
+    if (fits && tiles(128) >= cus) LAUNCH((gemm_tn_f32_mfma_kernel<128, 128>), 128, 256);
+    else if (fits && tiles(64) >= cus / 2) LAUNCH((gemm_tn_f32_mfma_kernel<64, 64>), 64, 256);
+    else if (R > 16 && Cc > 16 && tiles(32) >= 5 * (int64_t)cus / 8)
+        LAUNCH((gemm_tn_f32_split_kernel<32, 8, 4>), 32, 512);
+    else LAUNCH((gemm_tn_f32_split_kernel<16, 8, 4>), 16, 512);
+#undef LAUNCH
     return hipGetLastError();
 }
 

@@ -102,7 +102,7 @@ hipError_t launch_splitk_reduce(const float* P, int S, int64_t split_stride, int
                                 void* C, int64_t ldc, int R, int Cc, int out_bf16,
                                 hipStream_t stream);
 hipError_t launch_gemm_tn_f32(const float* A, int64_t lda, const float* B, int64_t ldb,
-                              float* C, int64_t ldc, int R, int Cc, int D, hipStream_t stream);
+                              float* C, int64_t ldc, int R, int Cc, int D, int cus, hipStream_t stream);
 
 // fp32 sums of the depth ranges of a 256 x 256 or 256 x 192 tiled product
 // (g.splits ranges requested; *ranges receives the number of non-empty ones),
@@ -114,7 +114,7 @@ hipError_t launch_gemm_tn_bf16_v3_ranges(const GemmArgs& g, bool upper, int* ran
 int autocorr_ranges(int64_t M, int64_t K, bool f32);
 size_t autocorr_workspace_bytes(int64_t M, int64_t K, bool f32);
 hipError_t launch_autocorr_update(const void* X, int64_t ldx, int M, int K, bool f32, bool normalize,
-                                  float alpha, float* C, int64_t ldc, void* workspace, hipStream_t stream);
+                                  float alpha, float* C, int64_t ldc, void* workspace, int cus, hipStream_t stream);
 size_t pca_workspace_bytes(int64_t K);
 bool pca_available();
 hipError_t launch_principal_components(const float* C, int64_t ldc, int K, int L, bool by_magnitude, void* Pt,
@@ -127,7 +127,7 @@ size_t symprod_workspace_bytes(int64_t K);
 hipError_t launch_transpose(const void* src, int64_t lds, int rows, int cols, void* dst, int64_t ldd, bool f32,
                             hipStream_t stream);
 hipError_t launch_symmetrized_product(const float* A, int64_t lda, const float* B, int64_t ldb, float* C,
-                                      int64_t ldc, int K, float alpha, float beta, void* workspace,
+                                      int64_t ldc, int K, float alpha, float beta, void* workspace, int cus,
                                       hipStream_t stream);
 
 // ---- MX-FP8 products (gemm_mxfp8.hip) ----------------------------------------
