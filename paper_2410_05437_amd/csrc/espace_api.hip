@@ -115,7 +115,7 @@ espace::WaitCfg wait_cfg() {
 
 // ---- planning ---------------------------------------------------------------
 
-enum Kind { KIND_TILED = 0, KIND_SKINNY = 1, KIND_F32 = 2, KIND_GEMV = 3, KIND_STREAM = 4 };
+enum Kind { KIND_TILED = 0, KIND_MID = 1, KIND_F32 = 2, KIND_GEMV = 3, KIND_STREAM = 4 };
 
 struct Plan {
     int kind = KIND_F32;
@@ -130,45 +130,6 @@ struct Plan {
 };
 
 int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
-
-Plan plan_skinny(int R, int Cc, int D, int cus) {
-    // Measured on the decode layers (N <= 32): a launch costs a few µs
-    // whatever its size, so the depth is split only when the tokens make
-    // each workgroup's loads heavy or the depth is very large; 8 waves with
-    // 6 loads in flight fit 48-step depths exactly; 32-row groups halve the
-    // token re-reads from L2 when there are 9 or more tokens.  With fewer
-    // 16-row groups than half the CUs (the projection,
-    // L = 1536 rows), two depth segments per MFMA operand double the
-    // workgroups in one launch (K = 4096: 5.6 against 7.5 µs; K = 11008:
-    // 12.5 against 17.6 µs with a three-way split), and with 9 to 16 tokens
-    // as two token groups of 8 sharing the weight operand (K = 4096: 7.9
-    // against 8.1 µs at 16 tokens, 7.4 against 7.8 at 12, with a two-way
-    // split and its reduction launch); with 128 or more groups
-    // one depth range is fastest up to 256 steps (K = 6144, L = 3686: 12.3
-    // against 17.6 µs with two ranges).
-    Plan p;
-    p.kind = KIND_SKINNY;
-    const int nb1 = ceil_div(Cc, 16);
-    const int steps = ceil_div(D, 32);
-    const int target = 2 * cus;
-    if (nb1 >= target) {
-        if (R > 8) p.tile = espace::SKINNY_RG2_W4;
-        else p.tile = (steps <= 48) ? espace::SKINNY_RG1_W8_U6 : espace::SKINNY_RG1_W8_U8;
-    } else if (R <= 16 && nb1 < cus / 2 && steps <= 384) {
-        if (R <= 8) p.tile = steps <= 128 ? espace::SKINNY_SEG2_W8_U8 : espace::SKINNY_SEG2_W16_U4;
-        else p.tile = steps <= 128 ? espace::SKINNY_SEG2_TG2_W8_U8 : espace::SKINNY_SEG2_TG2_W16_U4;
-    } else {
-        p.tile = espace::SKINNY_RG1_W8_U8;
-        int s = R > 8 ? 2 : 1;
-        // at most 128 KB of each 16 rows per workgroup beyond 256 steps
-        const int by_depth = (R > 8 || steps > 256) ? ceil_div(steps, 128) : 1;
-        if (by_depth > s) s = by_depth;
-        if (s > 1 && steps / s < 32) s = steps / 32 > 1 ? steps / 32 : 1;   // >= 4 steps per wave
-        p.splits = s;
-    }
-    if (p.splits > 1) p.partial_bytes = (size_t)p.splits * R * espace::splitk_ld(Cc) * sizeof(float);
-    return p;
-}
 
 struct TileShape { int tile, bm, bn, per_cu; double eff; };
 
@@ -245,7 +206,7 @@ Plan plan_tiled_one(int R, int Cc, int D, int cus, double* cost_out) {
     return best;
 }
 
-Plan plan_tiled(int R, int Cc, int D, int cus) {
+Plan plan_tiled(int R, int Cc, int D, int cus, double* cost_out) {
     // A product whose tiles leave the last round of workgroups partly empty
     // can run as two launches split by rows, each with whole rounds.  Taken
     // when the model prices it at least 3% cheaper, a launch counted as 3 µs
@@ -260,6 +221,7 @@ Plan plan_tiled(int R, int Cc, int D, int cus) {
     // last round runs at higher clocks than the model assumes.
     double cost = 0;
     Plan best = plan_tiled_one(R, Cc, D, cus, &cost);
+    *cost_out = cost;
     if (R > 32768) return best;   // many rounds: the last one's share is small
     constexpr double kLaunch = 110e3;
     double best_split = 0.97 * cost;
@@ -269,6 +231,7 @@ Plan plan_tiled(int R, int Cc, int D, int cus) {
         const Plan p2 = plan_tiled_one(R - r1, Cc, D, cus, &c2);
         if (c1 + c2 + kLaunch < best_split) {
             best_split = c1 + c2 + kLaunch;
+            *cost_out = best_split;
             best = p1;
             best.rows1 = r1;
             best.tile2 = p2.tile;
@@ -280,39 +243,84 @@ Plan plan_tiled(int R, int Cc, int D, int cus) {
     return best;
 }
 
-// 3 to 16 tokens on a weight of at least 16 rows per CU: the persistent
-// streaming kernel.  Measured on the Llama2-7B FFN up+gate layer (22016 x
-// 1536 folded weight, 22016 x 4096 dense weight) against the skinny MFMA
-// kernel: expansion 19.6 -> 14.6 µs at 8 tokens, 19.9 -> 15.1 at 16; dense
-// 45.2 -> 34.2 and 57.3 -> 36.0 µs.  The projections (1536 rows) stay on the
-// skinny kernel (5.8 against 6.6 µs at 8 tokens), one and two tokens on the
-// whole-row kernel (the streaming kernel: 12.9 -> 16.8 µs on the expansion).
+// 3 to 16 tokens on more rows of B than one round of the small-tile kernel's
+// widest tiles holds: the persistent streaming kernel, which balances groups
+// of 16 rows over the CUs (28000 x 1536 at 16 tokens 17.8 against 19.8 µs,
+// 32000 x 4096 48 against 52).  Below that the small tiles are level or
+// faster (22016 x 1536: 14.1 against 15.0, 12288 x 1536: 9.1 against 10.2, 9000
+// x 6144: 22.8 against 27.9).
 bool use_stream(int R, int Cc, int D) {
-    return R >= 3 && espace::stream_supported(R, D) && (int64_t)Cc >= 16 * (int64_t)device_cus();
+    return R >= 3 && espace::stream_supported(R, D) && (int64_t)Cc > 96 * (int64_t)device_cus();
 }
 
-Plan plan_tn(int64_t R, int64_t Cc, int64_t D, espace_dtype dt) {
-    if (dt == ESPACE_F32) return Plan{};
+// One or two tokens: whole-row streaming with bf16 dot products (D ≤ 4096 for
+// the short rows' form, else tokens in LDS), unless the rows are few and
+// long, where the small tiles split the depth over a workgroup's waves.  At
+// one token 1536 x 11008 9.9 against 10.9 µs, 2458 x 6144 8.7 against 9.6, but
+// 12288 x 4096 and longer weights within 6% either way; at two tokens 2458 x
+// 24576 26.4 against 32.5, 12288 x 4096 17.5 against 20.0, 6144 x 2458 8.3
+// against 8.9, but 22016 x 1536 14.2 against 13.5.
+bool use_gemv(int R, int Cc, int D) {
+    if (!espace::gemv_supported(R, D)) return false;
+    if (R == 1) return !(D > 4096 && Cc < 8192);
+    return !(Cc <= 16384 && (D > 4096 || (D > 2048 && Cc >= 4096)));
+}
+
+constexpr int kMidMaxTokens = 1024;
+
+Plan plan_mid(int R, int Cc, int D, int cus, double* us) {
+    Plan p;
+    p.kind = KIND_MID;
+    *us = espace::mid_plan(R, Cc, D, cus, &p.tile, &p.splits);
+    if (p.splits > 1) p.partial_bytes = (size_t)p.splits * R * espace::splitk_ld(Cc) * sizeof(float);
+    return p;
+}
+
+Plan plan_bf16(int R, int Cc, int D) {
+    const int cus = device_cus();
+    double us = 0;
     if (R <= 32) {
-        // One or two tokens: whole-row streaming with bf16 dot products
-        // (measured at N = 1 on every decode layer of the workloads: 2-22%
-        // faster than the MFMA kernel, e.g. the Llama2-7B up+gate expansion
-        // 15.5 -> 14.2 µs, its dense W 38.1 -> 33.6 µs, the GPT3-22B
-        // expansion at L = 2458 31.1 -> 24.4 µs; at N = 2 faster or within
-        // 0.5 µs; slower from 3 tokens on).
-        if (espace::gemv_supported((int)R, (int)D)) {
-            Plan g;
+        Plan g;
+        if (use_gemv(R, Cc, D)) {
             g.kind = KIND_GEMV;
             return g;
         }
-        if (use_stream((int)R, (int)Cc, (int)D)) {
-            Plan g;
+        if (use_stream(R, Cc, D)) {
             g.kind = KIND_STREAM;
             return g;
         }
-        return plan_skinny((int)R, (int)Cc, (int)D, device_cus());
+        return plan_mid(R, Cc, D, cus, &us);
     }
-    return plan_tiled((int)R, (int)Cc, (int)D, device_cus());
+    double cost = 0;
+    const Plan t = plan_tiled(R, Cc, D, cus, &cost);
+    if (R > kMidMaxTokens) return t;
+    // the tiled plan's price in µs: its units at the expand GEMM's rate, a
+    // launch and its ramp, and the reduction launch of a depth split (fitted
+    // to the same measurements as mid_plan's; 333 x 12288 x 1536 stays tiled,
+    // 23 against 34 µs, 128 x 12288 x 1536 does not, 21 against 15)
+    const double tiled_us = 5.0 + 0.95 * 27.3e-6 * cost + (t.splits > 1 ? 2.5 : 0.0);
+    const Plan m = plan_mid(R, Cc, D, cus, &us);
+    return us < tiled_us ? m : t;
+}
+
+// A product's plan depends on its sizes and the device's CUs alone; each
+// thread keeps the last ones it made (a call asks for the same few plans
+// several times: workspace size, layout of Z, launches).
+Plan plan_tn(int64_t R, int64_t Cc, int64_t D, espace_dtype dt) {
+    if (dt == ESPACE_F32) return Plan{};
+    struct Entry { int R = 0, Cc = 0, D = 0, cus = 0; Plan p; };
+    static thread_local Entry memo[64];
+    const int cus = device_cus();
+    const unsigned h = (unsigned)R * 2654435761u ^ (unsigned)Cc * 2246822519u ^ (unsigned)D * 3266489917u;
+    Entry& e = memo[(h >> 16) % 64];
+    if (e.R != R || e.Cc != Cc || e.D != D || e.cus != cus) {
+        e.p = plan_bf16((int)R, (int)Cc, (int)D);
+        e.R = (int)R;
+        e.Cc = (int)Cc;
+        e.D = (int)D;
+        e.cus = cus;
+    }
+    return e.p;
 }
 
 // ESPACE_PLAN_LOG=1 prints each product's plan to stderr (read once per process).
@@ -585,7 +593,7 @@ espace_status run_tn(const void* A, int64_t lda, const void* B, int64_t ldb, voi
         g.a_pairs = a_pairs;
         g.c_pairs = c_pairs;
         if (p.pair) g.epoch = next_epoch();
-        if ((a_pairs || c_pairs) && p.kind != KIND_TILED)
+        if ((a_pairs && p.kind != KIND_TILED) || (c_pairs && p.kind != KIND_TILED && p.kind != KIND_MID))
             return fail(ESPACE_ERR_HIP, "row-pair layout on a plan that does not take it");
         if (p.kind == KIND_TILED && p.rows1 > 0) {
             // rows [0, rows1), then the rest with its own tile plan (and its
@@ -603,8 +611,16 @@ espace_status run_tn(const void* A, int64_t lda, const void* B, int64_t ldb, voi
                 if (p.pair2) g.epoch = next_epoch();
                 e = launch_tiled(g, stream);
             }
-        } else if (p.kind == KIND_SKINNY) {
-            e = espace::launch_skinny_tn_bf16(g, stream);
+        } else if (p.kind == KIND_MID) {
+            if (espace::mid_supported(lda, ldb)) {
+                e = espace::launch_mid_tn_bf16(g, stream);
+            } else {
+                // leading dimensions past its 32-bit offsets
+                if (c_pairs) return fail(ESPACE_ERR_HIP, "row-pair layout on a plan that does not take it");
+                g.tile = espace::TILE_128x128;
+                g.splits = 1;
+                e = espace::launch_gemm_tn_bf16(g, stream);
+            }
         } else if (p.kind == KIND_GEMV) {
             e = espace::launch_gemv_tn_bf16(g, stream);
         } else if (p.kind == KIND_STREAM) {
@@ -623,9 +639,9 @@ espace_status run_tn(const void* A, int64_t lda, const void* B, int64_t ldb, voi
 // that operand (the load path of the CUs bounds these GEMMs; measured on the
 // Llama2-7B QKV layer with operands rotated through HBM: 196.7 -> 191.0 µs,
 // the GPT3-22B FFN-up layer at L = 2458: 1180 -> 1117 µs).
-// Taken for prefill when the projection is tiled (any depth split; its
-// output is written by the GEMM kernel, the pair combine or the reduction
-// pass) and every launch of the expand GEMM is a single-range launch of the
+// Taken for prefill when the projection is tiled or on small tiles (any depth
+// split; its output is written by the GEMM kernel, the pair combine or the
+// reduction pass) and every launch of the expand GEMM is a single-range launch of the
 // four-wave kernel.
 bool z_pairs(int64_t N, int64_t L, int64_t K, int64_t M, int64_t ldx, int64_t ldp, int64_t ldwf, int64_t ldy,
              espace_dtype dt) {
@@ -635,7 +651,8 @@ bool z_pairs(int64_t N, int64_t L, int64_t K, int64_t M, int64_t ldx, int64_t ld
     auto v3_single = [](int tile, int splits) {
         return splits == 1 && (tile == espace::TILE_256x256_W8T || tile == espace::TILE_256x192_W8);
     };
-    if (a.kind != KIND_TILED || b.kind != KIND_TILED) return false;
+    if ((a.kind != KIND_TILED && a.kind != KIND_MID) || b.kind != KIND_TILED) return false;
+    if (a.kind == KIND_MID && !espace::mid_supported(ldx, ldp)) return false;
     if (!v3_single(b.tile, b.splits) || (b.rows1 > 0 && !v3_single(b.tile2, b.splits2))) return false;
     // the kernels' 32-bit offsets (the register-staged fallback keeps plain layouts)
     const int64_t lim = (int64_t)1 << 31;

@@ -16,22 +16,6 @@ enum TileKind {
     TILE_256x256_W8T = 5,    // 8 waves as 4 x 2 (64 x 128 each)
     TILE_128x192 = 6,        // 8 waves as 4 x 2 (32 x 96 each)
     TILE_256x192_W8 = 7,     // 8 waves as 4 x 2 (64 x 96 each)
-    SKINNY_RG1_W4 = 10,
-    SKINNY_RG2_W4 = 11,
-    SKINNY_RG1_W8 = 12,
-    SKINNY_RG2_W8 = 13,
-    SKINNY_RG1_W4_U8 = 14,   // as above with 8 steps of loads in flight per wave
-    SKINNY_RG2_W4_U8 = 15,
-    SKINNY_RG1_W8_U8 = 16,
-    SKINNY_RG2_W8_U8 = 17,
-    SKINNY_RG1_W8_U6 = 18,   // 6 steps in flight (48-step depths split evenly over 8 waves)
-    SKINNY_RG2_W4_U6 = 19,
-    SKINNY_RG1_W16_U8 = 20,  // 16 waves: one workgroup keeps 128 steps in flight
-    SKINNY_RG1_W16_U4 = 21,
-    SKINNY_SEG2_W8_U8 = 22,  // 8 rows x 2 depth segments per MFMA operand, N <= 8
-    SKINNY_SEG2_W16_U4 = 23,
-    SKINNY_SEG2_TG2_W8_U8 = 24,   // the same with two groups of 8 tokens, N <= 16
-    SKINNY_SEG2_TG2_W16_U4 = 25,
 };
 
 // Limit of the bounded cross-workgroup waits and the device counter of the
@@ -87,7 +71,13 @@ hipError_t launch_gemm_tn_bf16_v2(const GemmArgs& g, hipStream_t stream);
 // hipErrorInvalidValue for products it does not take (other tiles, fp32
 // output, >= 2^31 elements).
 hipError_t launch_gemm_tn_bf16_v3(const GemmArgs& g, hipStream_t stream);
-hipError_t launch_skinny_tn_bf16(const GemmArgs& g, hipStream_t stream);
+// Small-tile product for a few to a few hundred tokens (tile: index of the
+// configuration mid_plan chose; splits > 1 needs `partial`).  mid_plan returns
+// the estimated time in us; mid_supported says whether the leading dimensions
+// fit its 32-bit offsets.
+double mid_plan(int R, int Cc, int D, int cus, int* config, int* splits);
+bool mid_supported(int64_t lda, int64_t ldb);
+hipError_t launch_mid_tn_bf16(const GemmArgs& g, hipStream_t stream);
 // Vector-ALU product for 1 <= R <= 2 tokens with whole-row streaming (tile,
 // splits, partial unused); gemv_supported says whether the tokens fit its LDS.
 bool gemv_supported(int R, int D);
