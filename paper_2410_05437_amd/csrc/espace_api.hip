@@ -309,17 +309,19 @@ Plan plan_bf16(int R, int Cc, int D) {
 Plan plan_tn(int64_t R, int64_t Cc, int64_t D, espace_dtype dt) {
     if (dt == ESPACE_F32) return Plan{};
     struct Entry { int R = 0, Cc = 0, D = 0, cus = 0; Plan p; };
-    static thread_local Entry memo[64];
+    struct Set { Entry e[4]; unsigned next = 0; };
+    static thread_local Set memo[16];
     const int cus = device_cus();
-    const unsigned h = (unsigned)R * 2654435761u ^ (unsigned)Cc * 2246822519u ^ (unsigned)D * 3266489917u;
-    Entry& e = memo[(h >> 16) % 64];
-    if (e.R != R || e.Cc != Cc || e.D != D || e.cus != cus) {
-        e.p = plan_bf16((int)R, (int)Cc, (int)D);
-        e.R = (int)R;
-        e.Cc = (int)Cc;
-        e.D = (int)D;
-        e.cus = cus;
-    }
+    const unsigned h = ((unsigned)R * 2654435761u) ^ ((unsigned)Cc * 2246822519u) ^ ((unsigned)D * 3266489917u);
+    Set& set = memo[(h >> 20) % 16];
+    for (const Entry& e : set.e)
+        if (e.R == R && e.Cc == Cc && e.D == D && e.cus == cus) return e.p;
+    Entry& e = set.e[set.next++ % 4];
+    e.p = plan_bf16((int)R, (int)Cc, (int)D);
+    e.R = (int)R;
+    e.Cc = (int)Cc;
+    e.D = (int)D;
+    e.cus = cus;
     return e.p;
 }
 
@@ -1198,12 +1200,16 @@ espace_status espace_projected_linear_mxfp8(const void* Xq, int64_t ldxq, const 
     ESPACE_TRY(check_alias(mat_range("Y", Y, N, ldy, ESPACE_BF16), ins, 7));
     ESPACE_TRY(check_alias(ins[6], ins, 6));
     ESPACE_TRY(check_device());
-    // Z's codes in row pairs (2 mx_cols(L) bytes per pair), then its scales
-    const int64_t ldzq = 2 * mx_cols(L), ldzs = mx_cols(L) / 32;
+    // Z's codes in row pairs (2 mx_cols(L) bytes per pair) for the tiled
+    // expansion, in plain rows for the small-tile one, whose loads are whole
+    // lines anyway; then its scales
+    const int pairs = espace::mx_small_config((int)N, (int)M, (int)L, device_cus(), 0) < 0;
+    const int64_t ldzq = (pairs ? 2 : 1) * mx_cols(L), ldzs = mx_cols(L) / 32;
     unsigned char* Zq = static_cast<unsigned char*>(workspace);
     unsigned char* Zs = Zq + align_ws((size_t)round_up(N, 2) * mx_cols(L));
-    ESPACE_TRY(mx_project_launch(Ptq, ldpq, Pts, ldps, Xq, ldxq, Xs, ldxs, Zq, ldzq, Zs, ldzs, K, L, N, stream, 1));
-    ESPACE_TRY(mx_expand_launch(Zq, ldzq, Zs, ldzs, Wfq, ldwq, Wfs, ldws, Y, ldy, M, L, N, stream, 1));
+    ESPACE_TRY(mx_project_launch(Ptq, ldpq, Pts, ldps, Xq, ldxq, Xs, ldxs, Zq, ldzq, Zs, ldzs, K, L, N, stream,
+                                 pairs));
+    ESPACE_TRY(mx_expand_launch(Zq, ldzq, Zs, ldzs, Wfq, ldwq, Wfs, ldws, Y, ldy, M, L, N, stream, pairs));
     return ok();
 }
 

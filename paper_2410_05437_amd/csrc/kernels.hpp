@@ -144,6 +144,13 @@ int mx_gemm_tile(int R, int C, int cus, int out_mx);
 // out_mx: write MX-FP8 (codes and scales along the columns) instead of bf16.
 // hipErrorInvalidValue when an operand spans 2^31 bytes or more.
 hipError_t launch_gemm_mx(const MxGemmArgs& a, int out_mx, int cus, hipStream_t stream);
+// The small-tile configuration launch_gemm_mx takes for these sizes (token
+// codes in plain rows), or -1: a tiled kernel.
+int mx_small_config(int R, int C, int D, int cus, int out_mx);
+// mid_mxfp8.hip: the cheapest small-tile configuration, -1 if none is
+// estimated below tiled_us; its launch.
+int mx_mid_config(int R, int C, int D, int cus, int out_mx, double tiled_us);
+hipError_t launch_mx_mid(const MxGemmArgs& a, int out_mx, int config, bool scales16, hipStream_t stream);
 hipError_t launch_mx_quantize(const uint16_t* A, int64_t lda, int R, int C, uint8_t* Q, int64_t ldq, uint8_t* S,
                               int64_t lds, hipStream_t stream);
 
