@@ -6,7 +6,9 @@
 // its first operand, so a lane ends with runs of 4 consecutive output columns
 // of one row, and the depth index of an operand is permuted the same way for
 // both: a lane's 16-byte chunk holds 4 consecutive k, chunk q of a row goes
-// to lane group q, and MFMA e of a slab takes element e of every chunk.
+// to lane group q, and MFMA e of a slab takes element e of every chunk.  The
+// sums of 32 (tiled) or 8 to 16 terms are formed apart and then added, so that
+// a long sum rounds at its full size that many times less often.
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -127,6 +129,7 @@ void gemm_tn_f32_mfma_kernel(const float* __restrict__ A, int64_t lda, const flo
         const unsigned char* pa = stage + (wr0 + lr) * (TK * 4);
         const unsigned char* pb = stage + (BM + wc0 + lr) * (TK * 4);
         const int left = D - t * TK;              // only the last step has fewer than TK
+        f32x16_t part[TM][TN];
 #pragma unroll
         for (int s = 0; s < TK / 8; ++s) {
             const int c = ((2 * s + lh) ^ sw) * 16;
@@ -151,8 +154,13 @@ void gemm_tn_f32_mfma_kernel(const float* __restrict__ A, int64_t lda, const flo
 #pragma unroll
                 for (int i = 0; i < TM; ++i)
 #pragma unroll
-                    for (int j = 0; j < TN; ++j) acc[i][j] = mfma_f32(fb[j][e], fa[i][e], acc[i][j]);
+                    for (int j = 0; j < TN; ++j)
+                        part[i][j] = mfma_f32(fb[j][e], fa[i][e], s == 0 && e == 0 ? f32x16_t{} : part[i][j]);
         }
+#pragma unroll
+        for (int i = 0; i < TM; ++i)
+#pragma unroll
+            for (int j = 0; j < TN; ++j) acc[i][j] += part[i][j];
     }
 #pragma unroll
     for (int i = 0; i < TM; ++i) {
@@ -210,9 +218,12 @@ void gemm_tn_f32_split_kernel(const float* __restrict__ A, int64_t lda, const fl
             }
         }
 #pragma unroll
-        for (int u = 0; u < UD; ++u)
+        for (int u = 0; u < UD; ++u) {
+            Acc part = {};
 #pragma unroll
-            for (int e = 0; e < 4; ++e) acc = mfma_f32(fb[u][e], fa[u][e], acc);
+            for (int e = 0; e < 4; ++e) part = mfma_f32(fb[u][e], fa[u][e], part);
+            acc += part;
+        }
     }
 #pragma unroll
     for (int q = 0; q < NQ; ++q) red[wave][q][lane] = f32x4_t{acc[4 * q], acc[4 * q + 1], acc[4 * q + 2], acc[4 * q + 3]};
