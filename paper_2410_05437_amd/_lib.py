@@ -25,6 +25,7 @@ _c_i64 = ctypes.c_int64
 _c_p = ctypes.c_void_p
 _c_sz = ctypes.c_size_t
 _c_int = ctypes.c_int
+_SIZE_MAX = ctypes.c_size_t(-1).value
 
 _SIGS = {
     # name: (argtypes, restype)
@@ -117,22 +118,55 @@ def _dt(t):
     raise TypeError(f"unsupported dtype {t.dtype}")
 
 
+# A decode layer runs in 15 to 30 us on the GPU, about what marshalling a call
+# cost (layer 17.7 us, MX-FP8 quantisation 12 and layer 24), so the helpers
+# below stay on plain integers and ask torch for as little as they can.
+
 def _mat(t, name):
     """(pointer, leading dimension) of a row-major 2-D tensor whose storage
     holds rows*ld elements (the library may read the padding of the last row)."""
-    if t.dim() != 2:
+    shape = t.shape
+    if len(shape) != 2:
         raise ValueError(f"{name} must be 2-D")
-    if t.stride(1) != 1 and t.shape[1] > 1:
+    rows, cols = shape
+    s0, s1 = t.stride()
+    if s1 != 1 and cols > 1:
         raise ValueError(f"{name} must have unit column stride")
-    ld = t.stride(0) if t.shape[0] > 1 else max(t.stride(0), t.shape[1])
-    need = (t.storage_offset() + t.shape[0] * ld) * t.element_size()
-    if t.numel() and t.untyped_storage().nbytes() < need:
-        raise ValueError(f"{name}: storage must hold rows*ld elements (use padded_empty)")
-    return ctypes.c_void_p(t.data_ptr()), ld
+    ld = s0 if rows > 1 else max(s0, cols)
+    # rows without padding end where the tensor's elements end
+    if (ld != cols or s0 != cols) and rows and cols:
+        need = (t.storage_offset() + rows * ld) * t.element_size()
+        if t.untyped_storage().nbytes() < need:
+            raise ValueError(f"{name}: storage must hold rows*ld elements (use padded_empty)")
+    return t.data_ptr(), ld
 
 
 def _stream(device):
-    return ctypes.c_void_p(torch.cuda.current_stream(device).cuda_stream)
+    """torch's current HIP stream on the device (a raw handle)."""
+    return torch._C._cuda_getCurrentRawStream(device.index)
+
+
+class _on:
+    """`with _on(device)`: that device current (as torch.cuda.device), without
+    the cost of switching when it already is."""
+    __slots__ = ("index", "prev")
+
+    def __init__(self, device):
+        if device.type != "cuda":
+            raise ValueError(f"Expected a cuda device, but got: {device}")
+        self.index = device.index
+
+    def __enter__(self):
+        prev = torch.cuda.current_device()
+        self.prev = -1
+        if prev != self.index:
+            torch.cuda.set_device(self.index)
+            self.prev = prev
+
+    def __exit__(self, *exc):
+        if self.prev >= 0:
+            torch.cuda.set_device(self.prev)
+        return False
 
 
 def padded_empty(rows, cols, dtype, device, align=8):
@@ -167,7 +201,7 @@ def _out(out, rows, cols, like, name):
 def espace_workspace_bytes(op, M, K, L, N, dtype):
     dt = BF16 if dtype == torch.bfloat16 else F32
     n = lib.espace_workspace_bytes(op, M, K, L, N, dt)
-    if n == ctypes.c_size_t(-1).value:
+    if n == _SIZE_MAX:
         raise EspaceError(2, "invalid sizes for workspace query")
     return n
 
@@ -194,9 +228,9 @@ def espace_fold_weights(W, Pt, Wf=None, workspace=None):
     pw, ldw = _mat(W, "W")
     pp, ldp = _mat(Pt, "Pt")
     po, ldo = _mat(Wf, "Wf")
-    with torch.cuda.device(W.device):
+    with _on(W.device):
         _check(lib.espace_fold_weights(pw, ldw, pp, ldp, po, ldo, M, K, L, _dt(W),
-                                       ctypes.c_void_p(ws.data_ptr() if ws is not None else 0),
+                                       ws.data_ptr() if ws is not None else 0,
                                        wsb, _stream(W.device)))
     return Wf
 
@@ -211,9 +245,9 @@ def espace_project(Pt, X, Z=None, workspace=None):
     pp, ldp = _mat(Pt, "Pt")
     px, ldx = _mat(X, "X")
     pz, ldz = _mat(Z, "Z")
-    with torch.cuda.device(X.device):
+    with _on(X.device):
         _check(lib.espace_project(pp, ldp, px, ldx, pz, ldz, K, L, N, _dt(X),
-                                  ctypes.c_void_p(ws.data_ptr() if ws is not None else 0),
+                                  ws.data_ptr() if ws is not None else 0,
                                   wsb, _stream(X.device)))
     return Z
 
@@ -228,9 +262,9 @@ def espace_expand(Z, Wf, Y=None, workspace=None):
     pz, ldz = _mat(Z, "Z")
     pw, ldw = _mat(Wf, "Wf")
     py, ldy = _mat(Y, "Y")
-    with torch.cuda.device(Z.device):
+    with _on(Z.device):
         _check(lib.espace_expand(pz, ldz, pw, ldw, py, ldy, M, L, N, _dt(Z),
-                                 ctypes.c_void_p(ws.data_ptr() if ws is not None else 0),
+                                 ws.data_ptr() if ws is not None else 0,
                                  wsb, _stream(Z.device)))
     return Y
 
@@ -247,9 +281,9 @@ def espace_projected_linear(X, Pt, Wf, Y=None, workspace=None):
     pp, ldp = _mat(Pt, "Pt")
     pw, ldw = _mat(Wf, "Wf")
     py, ldy = _mat(Y, "Y")
-    with torch.cuda.device(X.device):
+    with _on(X.device):
         _check(lib.espace_projected_linear(px, ldx, pp, ldp, pw, ldw, py, ldy, M, K, L, N, _dt(X),
-                                           ctypes.c_void_p(ws.data_ptr() if ws is not None else 0),
+                                           ws.data_ptr() if ws is not None else 0,
                                            wsb, _stream(X.device)))
     return Y
 
@@ -266,7 +300,7 @@ def espace_projected_linear_noalloc(X, Pt, Wf, Y):
     pp, ldp = _mat(Pt, "Pt")
     pw, ldw = _mat(Wf, "Wf")
     py, ldy = _mat(Y, "Y")
-    with torch.cuda.device(X.device):
+    with _on(X.device):
         _check(lib.espace_projected_linear_noalloc(px, ldx, pp, ldp, pw, ldw, py, ldy, M, K, L, N, _dt(X),
                                                    _stream(X.device)))
     return Y
@@ -282,9 +316,9 @@ def espace_dense_linear(X, W, Y=None, workspace=None):
     px, ldx = _mat(X, "X")
     pw, ldw = _mat(W, "W")
     py, ldy = _mat(Y, "Y")
-    with torch.cuda.device(X.device):
+    with _on(X.device):
         _check(lib.espace_dense_linear(px, ldx, pw, ldw, py, ldy, M, K, N, _dt(X),
-                                       ctypes.c_void_p(ws.data_ptr() if ws is not None else 0),
+                                       ws.data_ptr() if ws is not None else 0,
                                        wsb, _stream(X.device)))
     return Y
 
@@ -301,9 +335,9 @@ def espace_autocorrelation_update(X, C, alpha, normalize=False, workspace=None):
     ws, wsb = _ws(workspace, espace_workspace_bytes(OP_AUTOCORR, 0, K, 0, N, X.dtype), X.device)
     px, ldx = _mat(X, "X")
     pc, ldc = _mat(C, "C")
-    with torch.cuda.device(X.device):
+    with _on(X.device):
         _check(lib.espace_autocorrelation_update(px, ldx, pc, ldc, K, N, 1 if normalize else 0, float(alpha),
-                                                 _dt(X), ctypes.c_void_p(ws.data_ptr() if ws is not None else 0),
+                                                 _dt(X), ws.data_ptr() if ws is not None else 0,
                                                  wsb, _stream(X.device)))
     return C
 
@@ -328,9 +362,9 @@ def espace_symmetrized_product(A, B, C=None, workspace=None, alpha=1.0, beta=0.0
     pa, lda = _mat(A, "A")
     pb, ldb = _mat(B, "B")
     pc, ldc = _mat(C, "C")
-    with torch.cuda.device(A.device):
+    with _on(A.device):
         _check(lib.espace_symmetrized_product(pa, lda, pb, ldb, pc, ldc, K, float(alpha), float(beta),
-                                              ctypes.c_void_p(ws.data_ptr() if ws is not None else 0), wsb,
+                                              ws.data_ptr() if ws is not None else 0, wsb,
                                               _stream(A.device)))
     return C
 
@@ -361,18 +395,18 @@ def espace_principal_components(C, L, dtype=torch.bfloat16, Pt=None, eigenvalues
     ws, wsb = _ws(workspace, espace_workspace_bytes(OP_PCA, 0, K, L, 0, Pt.dtype), C.device)
     pc, ldc = _mat(C, "C")
     pp, ldp = _mat(Pt, "Pt")
-    with torch.cuda.device(C.device):
-        _check(lib.espace_principal_components(pc, ldc, pp, ldp, ctypes.c_void_p(eigenvalues.data_ptr()),
-                                               ctypes.c_void_p(info.data_ptr()), K, L, 1 if by_magnitude else 0,
+    with _on(C.device):
+        _check(lib.espace_principal_components(pc, ldc, pp, ldp, eigenvalues.data_ptr(),
+                                               info.data_ptr(), K, L, 1 if by_magnitude else 0,
                                                _dt(Pt),
-                                               ctypes.c_void_p(ws.data_ptr() if ws is not None else 0), wsb,
+                                               ws.data_ptr() if ws is not None else 0, wsb,
                                                _stream(C.device)))
     return Pt, eigenvalues, info
 
 
 def _opt_out(t, rows, cols, like, name, want):
     if not want:
-        return None, ctypes.c_void_p(0), 0
+        return None, 0, 0
     t = _out(t, rows, cols, like, name)
     p, ld = _mat(t, name)
     return t, p, ld
@@ -394,10 +428,10 @@ def espace_projected_linear_backward(dY, Z, Pt, Wf, dX=None, dW=None, want_dx=Tr
     pz, ldz = _mat(Z, "Z")
     pp, ldp = _mat(Pt, "Pt")
     pw, ldw = _mat(Wf, "Wf")
-    with torch.cuda.device(dY.device):
+    with _on(dY.device):
         _check(lib.espace_projected_linear_backward(pdy, lddy, pz, ldz, pp, ldp, pw, ldw, pdx, lddx, pdw, lddw,
                                                     M, K, L, N, _dt(dY),
-                                                    ctypes.c_void_p(ws.data_ptr() if ws is not None else 0), wsb,
+                                                    ws.data_ptr() if ws is not None else 0, wsb,
                                                     _stream(dY.device)))
     return dX, dW
 
@@ -414,9 +448,9 @@ def espace_dense_linear_backward(dY, X, W, dX=None, dW=None, want_dx=True, want_
     pdy, lddy = _mat(dY, "dY")
     px, ldx = _mat(X, "X")
     pw, ldw = _mat(W, "W")
-    with torch.cuda.device(dY.device):
+    with _on(dY.device):
         _check(lib.espace_dense_linear_backward(pdy, lddy, px, ldx, pw, ldw, pdx, lddx, pdw, lddw, M, K, N,
-                                                _dt(dY), ctypes.c_void_p(ws.data_ptr() if ws is not None else 0),
+                                                _dt(dY), ws.data_ptr() if ws is not None else 0,
                                                 wsb, _stream(dY.device)))
     return dX, dW
 
@@ -479,7 +513,7 @@ def espace_quantize_mxfp8(A, out=None):
     if out.device != A.device:
         raise ValueError("out and A must share a device")
     pa, lda = _mat(A, "A")
-    with torch.cuda.device(A.device):
+    with _on(A.device):
         _check(lib.espace_quantize_mxfp8(pa, lda, R, C, pq, ldq, ps, lds, _stream(A.device)))
     return out
 
@@ -493,7 +527,7 @@ def espace_project_mxfp8(Pt, X, Z=None):
     c = _mx(Z, "Z", N, L)
     if len({Pt.device, X.device, Z.device}) != 1:
         raise ValueError("operands must share a device")
-    with torch.cuda.device(X.device):
+    with _on(X.device):
         _check(lib.espace_project_mxfp8(*a, *b, *c, K, L, N, _stream(X.device)))
     return Z
 
@@ -510,7 +544,7 @@ def espace_expand_mxfp8(Z, Wf, Y=None):
     if Wf.device != Z.device:
         raise ValueError("operands must share a device")
     py, ldy = _mat(Y, "Y")
-    with torch.cuda.device(Z.device):
+    with _on(Z.device):
         _check(lib.espace_expand_mxfp8(*a, *b, py, ldy, M, L, N, _stream(Z.device)))
     return Y
 
@@ -531,8 +565,8 @@ def espace_projected_linear_mxfp8(X, Pt, Wf, Y=None, workspace=None):
     ws, wsb = _ws(workspace, espace_workspace_bytes(OP_PROJECTED_LINEAR_MXFP8, M, K, L, N, torch.bfloat16),
                   X.device)
     py, ldy = _mat(Y, "Y")
-    with torch.cuda.device(X.device):
+    with _on(X.device):
         _check(lib.espace_projected_linear_mxfp8(*a, *b, *c, py, ldy, M, K, L, N,
-                                                 ctypes.c_void_p(ws.data_ptr() if ws is not None else 0), wsb,
+                                                 ws.data_ptr() if ws is not None else 0, wsb,
                                                  _stream(X.device)))
     return Y
