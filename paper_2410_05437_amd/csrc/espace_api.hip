@@ -188,6 +188,11 @@ Plan plan_tiled_one(int R, int Cc, int D, int cus, double* cost_out) {
                 // a round runs per_cu blocks on every CU
                 const double per_round = (double)s.bm * s.bn * ceil_div(ktiles, splits) * s.per_cu;
                 double cost = rounds * per_round / s.eff;
+                // 128 x 192 tiles at long depths (gemm_bf16_v4.hip): a better
+                // rate and 6 µs of ramp and write-out per round (4096 x 1536:
+                // 55 µs at depth 4096, 131 at 11008; 12288 rows: 160)
+                if (s.tile == espace::TILE_128x192 && !pair && ceil_div(ktiles, splits) >= espace::V4_MIN_STEPS)
+                    cost = rounds * (per_round / 0.90 + 220e3);
                 // the pair hand-off prices at 1.6x its bytes (measured: the
                 // second half waits for the first's stores)
                 if (pair) cost += 3.2 * tiles * s.bm * s.bn * 4.0 * byte_cost;

@@ -310,6 +310,8 @@ void gemm_tn_bf16_v2_kernel(const uint16_t* __restrict__ A, int64_t lda,
     int kt_end = kt0 + ktiles_per_split;
     kt_end = kt_end < ktiles ? kt_end : ktiles;
 
+    const DepthOrder order(kt0, D / BK < kt_end ? D / BK : kt_end);
+
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wrow0 = (wave / WN) * T::WTM;
@@ -356,7 +358,7 @@ void gemm_tn_bf16_v2_kernel(const uint16_t* __restrict__ A, int64_t lda,
         // prologue: steps kt0 .. kt0+STAGES-1 fill the stages
 #pragma unroll
         for (int p = 0; p < STAGES; ++p)
-            if (kt0 + p < kt_end) issue<T, BM>(smem, A, B, ra, rb, off, wave, lane, kt0 + p, p, D);
+            if (kt0 + p < kt_end) issue<T, BM>(smem, A, B, ra, rb, off, wave, lane, order(kt0 + p), p, D);
         {
             const int newer = (kt_end - kt0 - 1) < (STAGES - 1) ? (kt_end - kt0 - 1) : (STAGES - 1);
             wait_steps<T>(newer);
@@ -386,7 +388,7 @@ void gemm_tn_bf16_v2_kernel(const uint16_t* __restrict__ A, int64_t lda,
                 __builtin_amdgcn_s_barrier();
                 // stage st held step kt; it now receives step kt+STAGES
                 if (kt + STAGES < kt_end)
-                    issue<T, BM>(smem, A, B, ra, rb, off, wave, lane, kt + STAGES, st, D);
+                    issue<T, BM>(smem, A, B, ra, rb, off, wave, lane, order(kt + STAGES), st, D);
                 st = (st + 1 == STAGES) ? 0 : st + 1;
                 read_frags<T>(smem, fa0, fb0, st, 0, a_off, b_off, lh, sw);
             }
@@ -527,8 +529,8 @@ void tile_dims(int tile, int* bm, int* bn) {
 
 // The tiles other than the hand-ordered kernel's: depth step 64.  256 x 128,
 // 128 x 256 and 128 x 128: four waves, 32 x 32 x 16 MFMA blocks, two LDS
-// stages.  128 x 192 (the Llama2-7B projection, 4096 x 1536 x 4096, one round
-// of 256 tiles): eight waves as 4 x 2 (32 x 96 each, 16 x 16 x 32 blocks) and
+// stages.  128 x 192 (long depths: gemm_bf16_v4.hip; measured on the Llama2-7B
+// projection, 4096 x 1536 x 4096, one round of 256 tiles): eight waves as 4 x 2 (32 x 96 each, 16 x 16 x 32 blocks) and
 // three stages — with operands streamed from HBM 67-69 us with four waves and
 // two stages, 58-60 with three stages, 57-58 with eight waves; four stages
 // were no faster, four waves with 16 x 16 x 32 blocks slower (75-80 us).
@@ -548,7 +550,11 @@ hipError_t launch_gemm_tn_bf16_v2(const GemmArgs& g, hipStream_t stream) {
         case TILE_256x128: return launch_v2<256, 128, 2, 2, 64, 2>(g, stream);
         case TILE_128x256: return launch_v2<128, 256, 2, 2, 64, 2>(g, stream);
         case TILE_128x128: return launch_v2<128, 128, 2, 2, 64, 2>(g, stream);
-        case TILE_128x192: return launch_v2<128, 192, 4, 2, 64, 3, 16>(g, stream);
+        case TILE_128x192:
+            // the depth-halving kernel from 48 steps per range on
+            if (!g.pair && ((g.D + 63) / 64 + g.splits - 1) / g.splits >= V4_MIN_STEPS)
+                return launch_gemm_tn_bf16_v4(g, stream);
+            return launch_v2<128, 192, 4, 2, 64, 3, 16>(g, stream);
         default: return hipErrorInvalidValue;
     }
 }

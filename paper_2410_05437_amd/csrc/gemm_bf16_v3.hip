@@ -72,6 +72,8 @@ void gemm_tn_bf16_v3_kernel(const uint16_t* __restrict__ A, int64_t lda,
     // the next item's first two steps can be loaded ahead
     const bool ahead_ok = MODE == V3_BF16 && (Cc & 7) == 0 && kt0 + 2 <= nfull;
 
+    const DepthOrder order(kt0, nfull);
+
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const int wrow0 = (wave >> 1) * V3_WT;
@@ -122,11 +124,11 @@ void gemm_tn_bf16_v3_kernel(const uint16_t* __restrict__ A, int64_t lda,
             // the half-stages may still be read by a wave finishing the previous item
             if (item != (int)blockIdx.x) __syncthreads();
             v3_offsets<C, 1, APAIR != 0>(voff, row0, col0, R, Cc, lda, ldb, wave, lane);
-            int later = v3_load_half<C, APAIR != 0>(smem, A, B, ra, rb, voff, wave, lane, kt0, 0, hs(0, 0), D);
-            later = v3_load_half<C, APAIR != 0>(smem, A, B, ra, rb, voff, wave, lane, kt0, 1, hs(0, 1), D);
+            int later = v3_load_half<C, APAIR != 0>(smem, A, B, ra, rb, voff, wave, lane, order(kt0), 0, hs(0, 0), D);
+            later = v3_load_half<C, APAIR != 0>(smem, A, B, ra, rb, voff, wave, lane, order(kt0), 1, hs(0, 1), D);
             if (nsteps > 1) {
-                later = v3_load_half<C, APAIR != 0>(smem, A, B, ra, rb, voff, wave, lane, kt0 + 1, 0, hs(1, 0), D);
-                later += v3_load_half<C, APAIR != 0>(smem, A, B, ra, rb, voff, wave, lane, kt0 + 1, 1, hs(1, 1), D);
+                later = v3_load_half<C, APAIR != 0>(smem, A, B, ra, rb, voff, wave, lane, order(kt0 + 1), 0, hs(1, 0), D);
+                later += v3_load_half<C, APAIR != 0>(smem, A, B, ra, rb, voff, wave, lane, order(kt0 + 1), 1, hs(1, 1), D);
             } else {
                 later = 0;
             }
@@ -152,10 +154,10 @@ void gemm_tn_bf16_v3_kernel(const uint16_t* __restrict__ A, int64_t lda,
         // through registers after the MFMAs; 0: none.
         auto load_kind = [&](int h, int& lkt) -> int {
             if (kt + 2 < kt_end) {
-                lkt = kt + 2;
+                lkt = order(kt + 2);
                 return lkt * V3_BK + 32 * h + 32 <= D ? 1 : 2;
             }
-            lkt = kt0 + (kt + 2 - kt_end);
+            lkt = order(kt0 + (kt + 2 - kt_end));
             if (!ahead_next) return 0;
             if (kt + 2 == kt_end && h == 0)
                 v3_offsets<C, 1, APAIR != 0>(voff, ntr * V3_BM, ntc * BN, R, Cc, lda, ldb, wave, lane);
@@ -205,22 +207,22 @@ void gemm_tn_bf16_v3_kernel(const uint16_t* __restrict__ A, int64_t lda,
         // two newer half-steps of loads in flight
         while (kt + 3 < nfull) {
             v3_substep<C, false, true, true, APAIR != 0>(acc, fa0, fb0, fa1, fb1, aA3, aB3, smem, A, B, ra, rb, voff,
-                                             wave, kt + 2, 0, hs(1, 0));
+                                             wave, order(kt + 2), 0, hs(1, 0));
             v3_wait_lgkm0();
             v3_wait_vm<2 * C::LPH>();
             __builtin_amdgcn_s_barrier();
             v3_substep<C, false, true, true, APAIR != 0>(acc, fa1, fb1, fa0, fb0, aA0, aB0, smem, A, B, ra, rb, voff,
-                                             wave, kt + 2, 1, hs(1, 1));
+                                             wave, order(kt + 2), 1, hs(1, 1));
             v3_wait_lgkm0();
             v3_wait_vm<2 * C::LPH>();
             __builtin_amdgcn_s_barrier();
             v3_substep<C, false, true, true, APAIR != 0>(acc, fa0, fb0, fa1, fb1, aA1, aB1, smem, A, B, ra, rb, voff,
-                                             wave, kt + 3, 0, hs(0, 0));
+                                             wave, order(kt + 3), 0, hs(0, 0));
             v3_wait_lgkm0();
             v3_wait_vm<2 * C::LPH>();
             __builtin_amdgcn_s_barrier();
             v3_substep<C, false, true, true, APAIR != 0>(acc, fa1, fb1, fa0, fb0, aA2, aB2, smem, A, B, ra, rb, voff,
-                                             wave, kt + 3, 1, hs(0, 1));
+                                             wave, order(kt + 3), 1, hs(0, 1));
             v3_wait_lgkm0();
             v3_wait_vm<2 * C::LPH>();
             __builtin_amdgcn_s_barrier();

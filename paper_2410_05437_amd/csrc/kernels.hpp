@@ -67,6 +67,10 @@ inline int64_t splitk_ld(int Cc) { return (Cc + 7) / 8 * 8; }
 
 hipError_t launch_gemm_tn_bf16(const GemmArgs& g, hipStream_t stream);
 hipError_t launch_gemm_tn_bf16_v2(const GemmArgs& g, hipStream_t stream);
+// 128 x 192 tiles at depths of V4_MIN_STEPS steps of 64 or more per range: eight
+// waves that halve every step.
+constexpr int V4_MIN_STEPS = 48;
+hipError_t launch_gemm_tn_bf16_v4(const GemmArgs& g, hipStream_t stream);
 // Four-wave 256 x 256 and 256 x 192 kernel with a hand-ordered main loop;
 // hipErrorInvalidValue for products it does not take (other tiles, fp32
 // output, >= 2^31 elements).

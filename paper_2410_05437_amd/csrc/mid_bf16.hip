@@ -18,7 +18,8 @@
 //  * A stage's rows are 128 bytes, whole cache lines; the waves' steps are
 //    neighbours, so together they read 512 bytes to 1 KB of a row.
 // Rates: 65 to 80 KB/us per CU through the load path, or 4.5 to 5.5 TB/s of B
-// from HBM.  Measured with operands rotated through HBM against the kernels
+// from HBM.  Each XCD starts at another depth (DepthOrder: 333 x 1536 x 11008
+// 33.0 -> 31.0 us, 48 x 12288 x 4096 22.5 -> 20.7).  Measured with operands rotated through HBM against the kernels
 // used before (an MFMA kernel loading straight to registers up to 32 tokens,
 // depth-split 128 x 192 tiles and a reduction pass above), us:
 //     tokens x rows of B x depth     before   now
@@ -134,12 +135,13 @@ void mid_tn_bf16_kernel(const uint16_t* __restrict__ A, int64_t lda, const uint1
     const int s0 = blockIdx.y * sps;
     const int ns = min(sps, steps - s0);          // steps of this depth range
     const int mine = ns > wave ? (ns - wave + W - 1) / W : 0;   // of this wave: s0 + wave, s0 + wave + W, ...
+    const DepthOrder order(0, ns > 0 ? ns : 0);   // the XCDs start at different depths
     // the loads of this wave's step t into stage st; past the depth they are
     // still issued, reading past the buffers, so that the count of loads in
     // flight is the same throughout
     auto issue = [&](int t, int st) {
         unsigned char* stage = ring + st * T::STAGE;
-        const int k0 = (s0 + t * W + wave) * MK;
+        const int k0 = (s0 + order(t * W + wave)) * MK;
         if (k0 + MK <= D) {
 #pragma unroll
             for (int j = 0; j < T::LPS; ++j)
@@ -188,7 +190,7 @@ void mid_tn_bf16_kernel(const uint16_t* __restrict__ A, int64_t lda, const uint1
 #pragma unroll
             for (int j = 0; j < T::TN; ++j) fb[s][j] = *reinterpret_cast<const u32x4_t*>(pb + at(j, s));
         }
-        const int left = D - (s0 + t * W + wave) * MK;
+        const int left = D - (s0 + order(t * W + wave)) * MK;
         if (left < MK) {
 #pragma unroll
             for (int s = 0; s < T::NS; ++s) {
