@@ -8,8 +8,8 @@
 //    are transposed (and scaled) into Xt[K][M] so that the sum over tokens is
 //    the contiguous dimension of a "TN" product Xt·Xtᵀ, which runs on the
 //    MFMA GEMM kernels with fp32 results per depth range; the product is
-//    symmetric, so (bf16) only the 256 x 256 tiles on and above the diagonal
-//    are computed, and a last pass adds alpha times the sum of the ranges to
+//    symmetric, so (bf16) only the tiles that reach the diagonal or lie above
+//    it are computed, and a last pass adds alpha times the sum of the ranges to
 //    C in fixed order, reading the mirrored entry below the diagonal tiles.
 //  * GO-MSE / NL-MSE candidates (Theorem 2): C = beta·C + alpha·(A·Bᵀ + B·Aᵀ),
 //    for the symmetric autocorrelations A = C_X and B = C_W (or, per
@@ -26,6 +26,7 @@
 //    positive.
 #include <dlfcn.h>
 #include <math.h>
+#include <algorithm>
 #include <mutex>
 
 #include <rocblas/rocblas.h>
@@ -191,44 +192,50 @@ __global__ __launch_bounds__(256) void transpose_scale_bf16_kernel(const uint16_
     }
 }
 
-// C[r][c] += alpha · Σ_s P_s[r][c], the depth ranges added in order.  With
-// tile > 0 only the tiles on and above the diagonal of P (tile x tile, a
-// multiple of 64) hold sums: a 64 x 64 block below them reads its mirror
-// block of P row by row and transposes the sums through LDS.
+// C[r][c] += alpha · Σ_s P_s[r][c], the depth ranges added in order; K x K.  With
+// bm > 0 only the bm x bn tiles of P that reach the diagonal or lie above it
+// hold sums (bm, bn multiples of 32): a 32 x 32 block below them reads its
+// mirror block of P and transposes the sums through LDS; a block on the
+// diagonal mirrors its own upper half, so C's update is exactly symmetric
+// whatever tiles P came from.  One 16-byte piece of
+// a row per thread.  Bound by memory at large K (4096: 34 us for P read and C
+// read and written); 32 x 32 blocks keep the chip busy at small K, where 64 x 64
+// blocks of 16 rows per thread took 68 us (K = 512, 16 ranges).
 __global__ __launch_bounds__(256) void accumulate_kernel(const float* __restrict__ P, int S, int64_t stride,
-                                                         int64_t ldp, float* __restrict__ C, int64_t ldc,
-                                                         int R, int Cc, float alpha, int tile) {
-    __shared__ float t[64][65];
-    const int r0 = blockIdx.y * 64, c0 = blockIdx.x * 64;
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    const bool mirror = tile > 0 && r0 / tile > c0 / tile;    // uniform over the block
-    if (!mirror) {
-        for (int i = ty; i < 64; i += 4) {
-            const int r = r0 + i, c = c0 + tx;
-            if (r >= R || c >= Cc) continue;
-            const int64_t at = (int64_t)r * ldp + c;
-            float s = 0.f;
-            for (int q = 0; q < S; ++q) s += P[q * stride + at];
-            float* o = C + (int64_t)r * ldc + c;
-            *o = fmaf(alpha, s, *o);
-        }
-        return;
+                                                         int64_t ldp, float* __restrict__ C, int64_t ldc, int K,
+                                                         float alpha, int bm, int bn) {
+    __shared__ float t[32][33];
+    const int r0 = blockIdx.y * 32, c0 = blockIdx.x * 32;
+    const int i = threadIdx.x >> 3, j = (threadIdx.x & 7) * 4;
+    const bool mirror = bm > 0 && upper_first(r0 / bm, bm, bn) > c0 / bn;    // uniform over the block
+    const int pr = (mirror ? c0 : r0) + i, pc = (mirror ? r0 : c0) + j;
+    f32x4_t s = {0.f, 0.f, 0.f, 0.f};
+    if (pr < K && pc < K) {
+        // P's rows are padded to 8: the piece stays inside the row
+        const float* p = P + (int64_t)pr * ldp + pc;
+#pragma unroll 4
+        for (int q = 0; q < S; ++q) s += *reinterpret_cast<const f32x4_t*>(p + q * stride);
     }
-    for (int i = ty; i < 64; i += 4) {
-        const int pr = c0 + i, pc = r0 + tx;    // P[pr][pc] is the mirror of C[pc][pr]
-        float s = 0.f;
-        if (pr < Cc && pc < R) {
-            const int64_t at = (int64_t)pr * ldp + pc;
-            for (int q = 0; q < S; ++q) s += P[q * stride + at];
-        }
-        t[i][tx] = s;
+    if (mirror || (bm > 0 && r0 == c0)) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t[j + e][i] = s[e];
+        __syncthreads();
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (mirror || i > j + e) s[e] = t[i][j + e];
     }
-    __syncthreads();
-    for (int i = ty; i < 64; i += 4) {
-        const int r = r0 + i, c = c0 + tx;
-        if (r >= R || c >= Cc) continue;
-        float* o = C + (int64_t)r * ldc + c;
-        *o = fmaf(alpha, t[tx][i], *o);
+    const int r = r0 + i, c = c0 + j;
+    if (r >= K || c >= K) return;
+    float* o = C + (int64_t)r * ldc + c;
+    if (c + 4 <= K) {
+        f32x4_t v = *reinterpret_cast<const f32x4_t*>(o);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = fmaf(alpha, s[e], v[e]);
+        *reinterpret_cast<f32x4_t*>(o) = v;
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (c + e < K) o[e] = fmaf(alpha, s[e], o[e]);
     }
 }
 
@@ -354,29 +361,59 @@ Solver& solver() {
 
 }  // namespace
 
-size_t autocorr_workspace_bytes(int64_t M, int64_t K, bool f32) {
+namespace {
+
+// How the bf16 update computes its upper triangle: on small tiles (config >= 0),
+// or on 256 x bn tiles; S depth ranges.
+struct AutocorrPlan { int config, bn, S; };
+
+AutocorrPlan autocorr_plan(int64_t M, int64_t K, int cus) {
+    // ranges of at least 16 steps of 64 tokens; no more than fill the chip
+    // once with 256 x 256 tiles (this bounds the workspace)
+    const int steps = (int)((M + 63) / 64);
+    const int most = std::max(1, std::min(256 / upper_tiles((int)K, 256, 256), steps / 16));
+    AutocorrPlan best{-1, 256, 1};
+    double best_us = 1e300;
+    // 256 x 256 or 256 x 192 tiles, as many ranges (a sum's error grows with the
+    // depth of its range): us per step, growing with the CUs at work (K = 4096,
+    // 8192 tokens: 136 tiles of 256 x 256 140 us, 197 of 256 x 192 112; K = 2048:
+    // 36 x 7 ranges of 256 x 256 fit the chip better than 53 x 7 of 256 x 192)
+    const int per = (steps + most - 1) / most;
+    const int S = (steps + per - 1) / per;                   // no empty range
+    for (int bn = 256; bn >= 192; bn -= 64) {
+        const int64_t items = (int64_t)upper_tiles((int)K, 256, bn) * S;
+        const int64_t rounds = (items + cus - 1) / cus;
+        const double active = std::min(1.0, (double)items / cus);
+        const double us = 8.0 + rounds * per * (bn == 256 ? 1.0 : 0.78) * std::max(1.1, 1.6 * active) +
+                          4e-6 * S * (double)K * K / 4.0;
+        if (us < best_us) {
+            best_us = us;
+            best = AutocorrPlan{-1, bn, S};
+        }
+    }
+    // small matrices: tiles of up to 112 x 96 give every CU work, and their waves
+    // split the depth (the whole update: K = 700, 1000 tokens 53 -> 14 us; K =
+    // 512, 16384 tokens 106 -> 34, of which the accumulation's share is 60)
+    if (K <= 2048) {
+        int config = 0, s = 1;
+        const double us = mid_plan((int)K, (int)K, (int)M, cus, &config, &s);
+        if (s <= most && us < best_us) best = AutocorrPlan{config, 0, s};
+    }
+    return best;
+}
+
+}  // namespace
+
+int autocorr_ranges(int64_t M, int64_t K, bool f32, int cus) { return f32 ? 1 : autocorr_plan(M, K, cus).S; }
+
+size_t autocorr_workspace_bytes(int64_t M, int64_t K, bool f32, int cus) {
     const int64_t ldt = (M + 7) / 8 * 8;
     size_t b = (size_t)K * ldt * (f32 ? 4 : 2);               // Xt
     b = (b + 255) / 256 * 256;
     b += (size_t)((M + 63) / 64 * 64) * 4;                    // inverse norms
     b = (b + 255) / 256 * 256;
-    b += (size_t)autocorr_ranges(M, K, f32) * K * splitk_ld((int)K) * 4;   // fp32 sums per depth range
+    b += (size_t)autocorr_ranges(M, K, f32, cus) * K * splitk_ld((int)K) * 4;   // fp32 sums per depth range
     return b;
-}
-
-int autocorr_ranges(int64_t M, int64_t K, bool f32) {
-    if (f32) return 1;
-    // enough depth ranges to give the chip up to 256 workgroups in one
-    // round, each range at least 16 steps of 64 tokens deep
-    const int64_t n = (K + 255) / 256;
-    const int64_t tiles = n * (n + 1) / 2;
-    const int64_t steps = (M + 63) / 64;
-    int64_t S = 256 / tiles;
-    if (S > steps / 16) S = steps / 16;
-    if (S < 1) S = 1;
-    // the GEMM uses ceil(steps / ceil(steps / S)) non-empty ranges
-    const int64_t per = (steps + S - 1) / S;
-    return (int)((steps + per - 1) / per);
 }
 
 hipError_t launch_autocorr_update(const void* X, int64_t ldx, int M, int K, bool f32, bool normalize,
@@ -390,7 +427,8 @@ hipError_t launch_autocorr_update(const void* X, int64_t ldx, int M, int K, bool
     off += (size_t)((M + 63) / 64 * 64) * 4;
     off = (off + 255) / 256 * 256;
     float* part = reinterpret_cast<float*>(ws + off);
-    const int S = autocorr_ranges(M, K, f32);
+    const AutocorrPlan plan = f32 ? AutocorrPlan{-1, 0, 1} : autocorr_plan(M, K, cus);
+    const int S = plan.S;
     const int64_t ldp = splitk_ld(K);
 
     if (normalize) {
@@ -426,16 +464,24 @@ hipError_t launch_autocorr_update(const void* X, int64_t ldx, int M, int K, bool
         g.R = K;
         g.Cc = K;
         g.D = M;
-        g.tile = TILE_256x256;
         g.splits = S;
         g.partial = part;
-        int used = 0;
-        e = launch_gemm_tn_bf16_v3_ranges(g, true, &used, stream);
-        if (e == hipSuccess && used != S) return hipErrorInvalidValue;
+        g.cus = cus;
+        if (plan.config >= 0) {
+            g.tile = plan.config;
+            e = launch_mid_tn_bf16_ranges(g, stream);
+        } else {
+            g.tile = plan.bn == 256 ? TILE_256x256 : TILE_256x192_W8;
+            int used = 0;
+            e = launch_gemm_tn_bf16_v3_ranges(g, true, &used, stream);
+            if (e == hipSuccess && used != S) return hipErrorInvalidValue;
+        }
     }
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(accumulate_kernel, dim3(ceil_div_i(K, 64), ceil_div_i(K, 64)), dim3(256), 0, stream, part,
-                       S, (int64_t)K * ldp, ldp, C, ldc, K, K, alpha, f32 ? 0 : 256);
+    // the small tiles: every 32 x 32 block on or above the diagonal holds sums
+    const int bm = f32 ? 0 : (plan.config >= 0 ? 32 : 256), bn = plan.config >= 0 ? 32 : plan.bn;
+    hipLaunchKernelGGL(accumulate_kernel, dim3(ceil_div_i(K, 32), ceil_div_i(K, 32)), dim3(256), 0, stream, part, S,
+                       (int64_t)K * ldp, ldp, C, ldc, K, alpha, bm, bn);
     return hipGetLastError();
 }
 

@@ -111,21 +111,21 @@ struct DepthOrder {
 
 // Output-tile coordinates of workgroup bid among tiles_r x tiles_c tiles.
 // map bit 0: skip the XCD remapping; bit 1: plain row-major order instead of
-// groups of GROUP tile-rows walked column by column; bit 3: only the tiles on
-// and above the diagonal of a square tiling (nblocks = n(n+1)/2 for
-// tiles_c = n), row by row.
+// groups of GROUP tile-rows walked column by column; bit 3: only the bm x bn
+// tiles that reach the diagonal of a square matrix or lie above it (nblocks =
+// upper_tiles), row by row.
 template <int GROUP>
 __device__ __forceinline__ void tile_coords(int bid, int nblocks, int tiles_c, int map,
-                                            int& tile_r, int& tile_c) {
+                                            int& tile_r, int& tile_c, int bm = 1, int bn = 1) {
     const int t = (map & 1) ? bid : xcd_contiguous(bid, nblocks);
     if (map & 8) {
         int r = 0, off = 0;
-        while (r < tiles_c - 1 && off + (tiles_c - r) <= t) {
-            off += tiles_c - r;
+        while (off + (tiles_c - upper_first(r, bm, bn)) <= t) {
+            off += tiles_c - upper_first(r, bm, bn);
             ++r;
         }
         tile_r = r;
-        tile_c = r + (t - off);
+        tile_c = upper_first(r, bm, bn) + (t - off);
         return;
     }
     if (map & 2) {

@@ -411,7 +411,7 @@ size_t ws_bytes(espace_op op, int64_t M, int64_t K, int64_t L, int64_t N, espace
         case ESPACE_OP_PROJECT: return N ? align_ws(plan_tn(N, L, K, dt).partial_bytes) : 0;
         case ESPACE_OP_EXPAND: return (N && M) ? align_ws(plan_tn(N, M, L, dt).partial_bytes) : 0;
         case ESPACE_OP_DENSE: return (N && M) ? align_ws(plan_tn(N, M, K, dt).partial_bytes) : 0;
-        case ESPACE_OP_AUTOCORR: return N ? align_ws(espace::autocorr_workspace_bytes(N, K, dt == ESPACE_F32)) : 0;
+        case ESPACE_OP_AUTOCORR: return N ? align_ws(espace::autocorr_workspace_bytes(N, K, dt == ESPACE_F32, device_cus())) : 0;
         case ESPACE_OP_PCA: return align_ws(espace::pca_workspace_bytes(K));
         case ESPACE_OP_SYMPRODUCT: return align_ws(espace::symprod_workspace_bytes(K));
         case ESPACE_OP_BACKWARD: return (N && M) ? bwd_layout(M, K, L, N, dt).total : 0;

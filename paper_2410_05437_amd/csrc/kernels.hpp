@@ -59,6 +59,16 @@ __host__ __device__ inline int64_t pair_offset(int64_t r, int64_t k, int64_t ld)
     return (r >> 1) * ld + (k >> 5) * 64 + (r & 1) * 32 + (k & 31);
 }
 
+// Tiles of bm x bn of an n x n matrix that reach the diagonal or lie above it:
+// the first such tile column of tile row r, and their number.
+__host__ __device__ inline int upper_first(int r, int bm, int bn) { return r * bm / bn; }
+inline int upper_tiles(int n, int bm, int bn) {
+    const int tr = (n + bm - 1) / bm, tc = (n + bn - 1) / bn;
+    int t = 0;
+    for (int r = 0; r < tr; ++r) t += tc - upper_first(r, bm, bn);
+    return t;
+}
+
 // Tile size of a TileKind in the pair-combine kernel (rows, columns).
 void tile_dims(int tile, int* bm, int* bn);
 
@@ -91,6 +101,10 @@ hipError_t launch_gemv_tn_bf16(const GemmArgs& g, hipStream_t stream);
 // says whether the tokens and depth fit (depth up to 6144).
 bool stream_supported(int R, int D);
 hipError_t launch_stream_tn_bf16(const GemmArgs& g, hipStream_t stream);
+// Upper triangle of a symmetric product (A = B): fp32 sums of g.splits depth ranges
+// at g.partial + s * R * splitk_ld(Cc), not combined; the 32 x 32 blocks wholly
+// below the diagonal may not be computed.
+hipError_t launch_mid_tn_bf16_ranges(const GemmArgs& g, hipStream_t stream);
 // out_bf16: 0 fp32 output, 1 bf16, 2 bf16 in the row-pair layout
 hipError_t launch_splitk_reduce(const float* P, int S, int64_t split_stride, int64_t ldp,
                                 void* C, int64_t ldc, int R, int Cc, int out_bf16,
@@ -100,13 +114,13 @@ hipError_t launch_gemm_tn_f32(const float* A, int64_t lda, const float* B, int64
 
 // fp32 sums of the depth ranges of a 256 x 256 or 256 x 192 tiled product
 // (g.splits ranges requested; *ranges receives the number of non-empty ones),
-// range s at g.partial + s * R * splitk_ld(Cc); not combined.  upper (square
-// 256 x 256 tiling only): just the tiles on and above the diagonal.
+// range s at g.partial + s * R * splitk_ld(Cc); not combined.  upper (R == Cc):
+// just the tiles that reach the diagonal or lie above it.
 hipError_t launch_gemm_tn_bf16_v3_ranges(const GemmArgs& g, bool upper, int* ranges, hipStream_t stream);
 
 // Calibration (autocorrelation of calibration tokens, principal components).
-int autocorr_ranges(int64_t M, int64_t K, bool f32);
-size_t autocorr_workspace_bytes(int64_t M, int64_t K, bool f32);
+int autocorr_ranges(int64_t M, int64_t K, bool f32, int cus);
+size_t autocorr_workspace_bytes(int64_t M, int64_t K, bool f32, int cus);
 hipError_t launch_autocorr_update(const void* X, int64_t ldx, int M, int K, bool f32, bool normalize,
                                   float alpha, float* C, int64_t ldc, void* workspace, int cus, hipStream_t stream);
 size_t pca_workspace_bytes(int64_t K);

@@ -103,12 +103,15 @@ template <int BM, int BN, int W, int ST, int SEG>
 __global__ __launch_bounds__(W * 64, W / 4)
 void mid_tn_bf16_kernel(const uint16_t* __restrict__ A, int64_t lda, const uint16_t* __restrict__ B, int64_t ldb,
                         uint16_t* __restrict__ C, int64_t ldc, int R, int Cc, int D, int tiles_c, int c_pairs,
-                        float* __restrict__ part, int64_t ldp, int64_t split_stride, int sps) {
+                        float* __restrict__ part, int64_t ldp, int64_t split_stride, int sps, int upper) {
     using T = MidCfg<BM, BN, W, ST, SEG>;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[T::SMEM];
     int tile_r, tile_c;
     tile_coords<8>(blockIdx.x, gridDim.x, tiles_c, 0, tile_r, tile_c);
     const int row0 = tile_r * BM, col0 = tile_c * BN;
+    // a symmetric product: nothing of the tile lies in a 32 x 32 block on or above
+    // the diagonal
+    if (upper && row0 / 32 > (col0 + BN - 1) / 32) return;
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     unsigned char* ring = smem + wave * ST * T::STAGE;
@@ -259,16 +262,16 @@ void mid_tn_bf16_kernel(const uint16_t* __restrict__ A, int64_t lda, const uint1
 }
 
 template <int BM, int BN, int W, int ST, int SEG>
-hipError_t launch_cfg_mid(const GemmArgs& g, hipStream_t stream) {
+hipError_t launch_cfg_mid(const GemmArgs& g, bool upper, hipStream_t stream) {
     const int tr = (g.R + BM - 1) / BM, tc = (g.Cc + BN - 1) / BN;
     const int steps = (g.D + MK - 1) / MK;
     const int S = g.splits > 1 ? g.splits : 1;
     const int64_t ldp = splitk_ld(g.Cc), stride = (int64_t)g.R * ldp;
     hipLaunchKernelGGL((mid_tn_bf16_kernel<BM, BN, W, ST, SEG>), dim3(tr * tc, S), dim3(W * 64), 0, stream, g.A,
                        g.lda, g.B, g.ldb, (uint16_t*)g.C, g.ldc, g.R, g.Cc, g.D, tc, g.c_pairs,
-                       S > 1 ? g.partial : nullptr, ldp, stride, (steps + S - 1) / S);
+                       S > 1 || upper ? g.partial : nullptr, ldp, stride, (steps + S - 1) / S, upper ? 1 : 0);
     const hipError_t e = hipGetLastError();
-    if (e != hipSuccess || S == 1) return e;
+    if (e != hipSuccess || S == 1 || upper) return e;
     return launch_splitk_reduce(g.partial, S, stride, ldp, g.C, g.ldc, g.R, g.Cc, g.c_pairs ? 2 : 1, stream);
 }
 
@@ -313,14 +316,23 @@ bool mid_supported(int64_t lda, int64_t ldb) {
     return std::max(lda, ldb) * kMidMaxRows * 2 < ((int64_t)1 << 31);
 }
 
-hipError_t launch_mid_tn_bf16(const GemmArgs& g, hipStream_t stream) {
-    if (!mid_supported(g.lda, g.ldb) || g.a_pairs || g.c_f32) return hipErrorInvalidValue;
+static hipError_t launch_config(const GemmArgs& g, bool upper, hipStream_t stream) {
     int i = 0;
 #define X(BM, BN, W, ST, SEG) \
-    if (g.tile == i++) return launch_cfg_mid<BM, BN, W, ST, SEG>(g, stream);
+    if (g.tile == i++) return launch_cfg_mid<BM, BN, W, ST, SEG>(g, upper, stream);
     MID_CONFIGS(X)
 #undef X
     return hipErrorInvalidValue;
+}
+
+hipError_t launch_mid_tn_bf16(const GemmArgs& g, hipStream_t stream) {
+    if (!mid_supported(g.lda, g.ldb) || g.a_pairs || g.c_f32) return hipErrorInvalidValue;
+    return launch_config(g, false, stream);
+}
+
+hipError_t launch_mid_tn_bf16_ranges(const GemmArgs& g, hipStream_t stream) {
+    if (!mid_supported(g.lda, g.ldb) || g.R != g.Cc || !g.partial) return hipErrorInvalidValue;
+    return launch_config(g, true, stream);
 }
 
 }  // namespace espace
