@@ -171,6 +171,8 @@ Plan plan_tiled_one(int R, int Cc, int D, int cus, double* cost_out) {
         {espace::TILE_128x256, 128, 256, 1, 0.85},
         {espace::TILE_128x128, 128, 128, 2, 0.70},
         {espace::TILE_128x192, 128, 192, 1, 0.70},
+        {espace::TILE_192x192, 192, 192, 1, 0.95},
+        {espace::TILE_256x160, 256, 160, 1, 0.95},
     };
     const int ktiles = ceil_div(D, 64);
     const double byte_cost = 315.0 / (2.0 * 64 * cus);   // bytes priced against the MFMA rate
@@ -182,7 +184,8 @@ Plan plan_tiled_one(int R, int Cc, int D, int cus, double* cost_out) {
         const int64_t slots = (int64_t)cus * s.per_cu;
         for (int splits = 1; splits <= 4; ++splits) {
             if (splits > 1 && ktiles / splits < 8) break;
-            for (int pair = 0; pair <= (splits == 2 ? 1 : 0); ++pair) {
+            const bool halving = s.tile == espace::TILE_192x192 || s.tile == espace::TILE_256x160;
+            for (int pair = 0; pair <= (splits == 2 && !halving ? 1 : 0); ++pair) {
                 const int64_t blocks = tiles * splits;
                 const int64_t rounds = (blocks + slots - 1) / slots;
                 // a round runs per_cu blocks on every CU
@@ -193,6 +196,7 @@ Plan plan_tiled_one(int R, int Cc, int D, int cus, double* cost_out) {
                 // 55 µs at depth 4096, 131 at 11008; 12288 rows: 160)
                 if (s.tile == espace::TILE_128x192 && !pair && ceil_div(ktiles, splits) >= espace::V4_MIN_STEPS)
                     cost = rounds * (per_round / 0.90 + 220e3);
+                if (halving) cost += rounds * 220e3;
                 // the pair hand-off prices at 1.6x its bytes (measured: the
                 // second half waits for the first's stores)
                 if (pair) cost += 3.2 * tiles * s.bm * s.bn * 4.0 * byte_cost;
@@ -564,6 +568,11 @@ hipError_t launch_tiled(const GemmArgs& g, hipStream_t stream) {
         // register-staged kernel with 64-bit offsets (plain layouts only)
         const hipError_t e = espace::launch_gemm_tn_bf16_v3(g, stream);
         if (e == hipErrorInvalidValue && !g.a_pairs && !g.c_pairs) return espace::launch_gemm_tn_bf16(g, stream);
+        return e;
+    }
+    if (g.tile == espace::TILE_192x192 || g.tile == espace::TILE_256x160) {
+        const hipError_t e = espace::launch_gemm_tn_bf16_v4(g, stream);
+        if (e == hipErrorInvalidValue && !g.c_pairs) return espace::launch_gemm_tn_bf16(g, stream);
         return e;
     }
     return espace::launch_gemm_tn_bf16_v2(g, stream);

@@ -1,25 +1,30 @@
-// Tiled bfloat16 "TN" GEMM for tiles of 128 x 192 at long depths (one round of
-// 256 tiles on the Llama2-7B projections, 4096 x 1536):
+// Tiled bfloat16 "TN" GEMM whose waves split the tile and every depth step:
 //
 //     C[r][c] = sum_k A[r][k] * B[c][k]        (fp32 accumulation)
 //
 // Eight waves, two per SIMD, as 2 x 2 over the tile and 2 over the depth: of
 // every 64-deep step the waves of half h take the 32 of chunks 4 h .. 4 h + 3
-// for their 64 x 96 part of the tile (24 v_mfma_f32_16x16x32_bf16).  Against
-// eight waves of 32 x 96 (gemm_bf16_v2.hip) a step reads 80 KB of fragments
-// from LDS instead of 128 KB, which together with the 40 KB written bounded
-// that kernel; the halves' sums are added through LDS at the end, each wave
-// finishing every other block.  Four LDS stages (all 160 KB); one step of
-// fragments is read ahead into registers, one barrier per step.
-//
-// Bound by the operands through each CU's load path: the same loads without
-// arithmetic take 48 of the 55 us at depth 4096, the arithmetic alone 40, the
-// LDS reads alone 22 (10 of each are launch, ramp and writing the tile).
-// Measured (operands rotated through HBM): 4096 x 1536 x 4096 64 -> 56 us, x
-// 11008 156 -> 131, x 12288 163 -> 146 (before: eight waves of 32 x 96, or two
-// depth halves of 256 x 192 tiles combined in the kernel).  Three stages are
-// 2 us slower at depth 4096; below about 48 steps the sums' exchange costs
-// more than the loop gains (512 x 12288 x 1536: 27.0 against 25.4 us).
+// for their quarter of the tile (v_mfma_f32_16x16x32_bf16).  Against eight
+// waves spread over the tile a step reads far fewer fragment bytes from LDS
+// (128 x 192: 80 KB instead of 128, which with the 40 KB written bounded the
+// kernel of gemm_bf16_v2.hip); rows are 128 bytes, one request per cache line
+// (the four-wave kernel of gemm_bf16_v3.hip makes two).  One barrier per step.
+// The halves' sums are added through LDS at the end, each wave finishing every
+// other block.  Operands rotated through HBM, us:
+//  * 128 x 192, long depths (one round of 256 tiles on the Llama2-7B
+//    projections): four LDS stages (all 160 KB), one step of fragments read
+//    ahead.  4096 x 1536 x 4096 64 -> 56, x 11008 156 -> 131, x 12288 163 -> 146.
+//    Bound by the operands through each CU's load path: the same loads without
+//    arithmetic take 48 of the 55 at depth 4096, the arithmetic alone 40, the
+//    LDS reads alone 22 (10 of each are launch, ramp and writing the tile).
+//    Three stages: 2 more.  Below about 48 steps the sums' exchange costs more
+//    than the loop gains (512 x 12288 x 1536: 27.0 against 25.4).
+//  * 192 x 192 and 256 x 160, where they fill the chip's rounds better than
+//    256 x 256, 256 x 192 or 128 x 192: too many accumulators for reading
+//    ahead, so the two halves alternate between reading and multiplying.  12288 x
+//    1536 x 4096 153 -> 140 (512 tiles of 192 x 192), 8192 x 2458 x 24576 926 -> 885
+//    (512 of 256 x 160), 333 x 24576 x 2458 61 -> 56.  At equal rounds the
+//    four-wave kernel's larger tiles are 10 to 25% faster.
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -51,7 +56,7 @@ __device__ __forceinline__ void d_barrier() { asm volatile("s_waitcnt lgkmcnt(0)
 // part != nullptr: depth range blockIdx.y (`sps` steps) as fp32 sums at part +
 // blockIdx.y * split_stride, leading dimension ldp; else C in bf16, c_pairs in
 // the row-pair layout.
-template <int BM, int BN, int ST>
+template <int BM, int BN, int ST, bool AHEAD>
 __global__ __launch_bounds__(512, 2)
 void gemm_tn_bf16_v4_kernel(const uint16_t* __restrict__ A, int64_t lda, const uint16_t* __restrict__ B, int64_t ldb,
                             uint16_t* __restrict__ C, int64_t ldc, int R, int Cc, int D, int tiles_c, int c_pairs,
@@ -125,7 +130,8 @@ void gemm_tn_bf16_v4_kernel(const uint16_t* __restrict__ A, int64_t lda, const u
     for (int i = 0; i < TM; ++i)
 #pragma unroll
         for (int j = 0; j < TN; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
-    u32x4_t fa[2][TM], fb[2][TN];
+    constexpr int NF = AHEAD ? 2 : 1;             // fragment buffers
+    u32x4_t fa[NF][TM], fb[NF][TN];
     auto read = [&](int buf, int st) {
         const unsigned char* s = smem + st * T::STAGE;
 #pragma unroll
@@ -150,29 +156,61 @@ void gemm_tn_bf16_v4_kernel(const uint16_t* __restrict__ A, int64_t lda, const u
                 acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(as_bf16x8(fb[buf][j]), as_bf16x8(fa[buf][i]),
                                                                     acc[i][j], 0, 0, 0);
     };
-    // stages hold steps kt .. kt + ST - 1; one step of fragments is read ahead
-#pragma unroll
-    for (int p = 0; p < ST; ++p) issue(kt0 + p, p);
-    d_wait_vm<(ST - 1) * T::LPW>();
-    d_barrier();
-    read(0, 0);
     int st = 0;
-    auto step = [&](int buf, int kt) {
-        // stage of kt + 1 landed for this wave; after the barrier for all,
-        // and every wave has its fragments of step kt: its stage is free
-        d_wait_vm<(ST - 2) * T::LPW>();
+    if constexpr (AHEAD) {
+        // stages hold steps kt .. kt + ST - 1; one step of fragments is read ahead
+#pragma unroll
+        for (int p = 0; p < ST; ++p) issue(kt0 + p, p);
+        d_wait_vm<(ST - 1) * T::LPW>();
         d_barrier();
-        issue(kt + ST, st);
-        st = st + 1 == ST ? 0 : st + 1;
-        read(buf ^ 1, st);
-        mfmas(buf, kt);
-    };
-    int kt = kt0;
-    for (; kt + 1 < kt_end; kt += 2) {
-        step(0, kt);
-        step(1, kt + 1);
+        read(0, 0);
+        auto step = [&](int buf, int kt) {
+            // this wave's loads of step kt + 1 have landed; after the barrier
+            // every wave's, and every wave has its fragments of step kt: its
+            // stage is free
+            d_wait_vm<(ST - 2) * T::LPW>();
+            d_barrier();
+            issue(kt + ST, st);
+            st = st + 1 == ST ? 0 : st + 1;
+            read(buf ^ 1, st);
+            mfmas(buf, kt);
+        };
+        int kt = kt0;
+        for (; kt + 1 < kt_end; kt += 2) {
+            step(0, kt);
+            step(1, kt + 1);
+        }
+        if (kt < kt_end) step(0, kt);
+    } else {
+        // one fragment buffer: the waves of the first half read a step, then
+        // multiply it; those of the second multiply the step before while the
+        // others read, then read theirs
+#pragma unroll
+        for (int p = 0; p < ST - 1; ++p) issue(kt0 + p, p);
+        auto phase = [&](int kt) {
+            // step kt has landed for this wave, after the barrier for all, and
+            // every wave is done reading step kt - 1, whose stage is refilled
+            d_wait_vm<(ST - 2) * T::LPW>();
+            d_barrier();
+            issue(kt + ST - 1, st == 0 ? ST - 1 : st - 1);
+        };
+        if (half == 0) {
+            for (int kt = kt0; kt < kt_end; ++kt) {
+                phase(kt);
+                read(0, st);
+                st = st + 1 == ST ? 0 : st + 1;
+                mfmas(0, kt);
+            }
+        } else {
+            for (int kt = kt0; kt < kt_end; ++kt) {
+                phase(kt);
+                if (kt > kt0) mfmas(0, kt - 1);
+                read(0, st);
+                st = st + 1 == ST ? 0 : st + 1;
+            }
+            if (kt_end > kt0) mfmas(0, kt_end - 1);
+        }
     }
-    if (kt < kt_end) step(0, kt);
     d_wait_vm<0>();
     __syncthreads();
 
@@ -213,13 +251,13 @@ void gemm_tn_bf16_v4_kernel(const uint16_t* __restrict__ A, int64_t lda, const u
         }
 }
 
-template <int BM, int BN, int ST>
+template <int BM, int BN, int ST, bool AHEAD>
 hipError_t launch_cfg_v4(const GemmArgs& g, hipStream_t stream) {
     const int tr = (g.R + BM - 1) / BM, tc = (g.Cc + BN - 1) / BN;
     const int steps = (g.D + DK - 1) / DK;
     const int S = g.splits > 1 ? g.splits : 1;
     const int64_t ldp = splitk_ld(g.Cc), stride = (int64_t)g.R * ldp;
-    hipLaunchKernelGGL((gemm_tn_bf16_v4_kernel<BM, BN, ST>), dim3(tr * tc, S), dim3(512), 0, stream, g.A, g.lda, g.B,
+    hipLaunchKernelGGL((gemm_tn_bf16_v4_kernel<BM, BN, ST, AHEAD>), dim3(tr * tc, S), dim3(512), 0, stream, g.A, g.lda, g.B,
                        g.ldb, (uint16_t*)g.C, g.ldc, g.R, g.Cc, g.D, tc, g.c_pairs, S > 1 ? g.partial : nullptr, ldp,
                        stride, (steps + S - 1) / S);
     const hipError_t e = hipGetLastError();
@@ -233,7 +271,12 @@ hipError_t launch_gemm_tn_bf16_v4(const GemmArgs& g, hipStream_t stream) {
     const int64_t lim = (int64_t)1 << 31;
     if ((int64_t)g.R * g.lda >= lim || (int64_t)g.Cc * g.ldb >= lim || g.a_pairs || g.pair || g.c_f32)
         return hipErrorInvalidValue;
-    return launch_cfg_v4<128, 192, 4>(g, stream);
+    switch (g.tile) {
+        case TILE_128x192: return launch_cfg_v4<128, 192, 4, true>(g, stream);
+        case TILE_192x192: return launch_cfg_v4<192, 192, 3, false>(g, stream);
+        case TILE_256x160: return launch_cfg_v4<256, 160, 3, false>(g, stream);
+        default: return hipErrorInvalidValue;
+    }
 }
 
 }  // namespace espace

@@ -16,6 +16,8 @@ enum TileKind {
     TILE_256x256_W8T = 5,    // 8 waves as 4 x 2 (64 x 128 each)
     TILE_128x192 = 6,        // 8 waves as 4 x 2 (32 x 96 each)
     TILE_256x192_W8 = 7,     // 8 waves as 4 x 2 (64 x 96 each)
+    TILE_192x192 = 8,        // 8 waves as 2 x 2 x 2 depth halves
+    TILE_256x160 = 9,
 };
 
 // Limit of the bounded cross-workgroup waits and the device counter of the
@@ -77,8 +79,9 @@ inline int64_t splitk_ld(int Cc) { return (Cc + 7) / 8 * 8; }
 
 hipError_t launch_gemm_tn_bf16(const GemmArgs& g, hipStream_t stream);
 hipError_t launch_gemm_tn_bf16_v2(const GemmArgs& g, hipStream_t stream);
-// 128 x 192 tiles at depths of V4_MIN_STEPS steps of 64 or more per range: eight
-// waves that halve every step.
+// Eight waves that halve every step: 192 x 192 and 256 x 160 tiles, and 128 x 192
+// ones at V4_MIN_STEPS steps of 64 or more per range.  hipErrorInvalidValue for
+// 2^31 elements or more.
 constexpr int V4_MIN_STEPS = 48;
 hipError_t launch_gemm_tn_bf16_v4(const GemmArgs& g, hipStream_t stream);
 // Four-wave 256 x 256 and 256 x 192 kernel with a hand-ordered main loop;
