@@ -215,7 +215,7 @@ void gemm_mx_z_kernel(MxGemmArgs a) {
     using C = MxZCfg<BT, BW, NS, SS>;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[C::SMEM];
 
-    const int tiles_c = (a.C + BW - 1) / BW;
+    const int tiles_c = (a.cpad + BW - 1) / BW;   // the padding columns are written too
     const int tiles = tiles_c * ((a.R + BT - 1) / BT);
     int tile_r, tile_c;
     tile_coords<8>(blockIdx.x, tiles, tiles_c, 0, tile_r, tile_c);
@@ -882,7 +882,7 @@ hipError_t launch_pipelined(const MxGemmArgs& a, int cus, hipStream_t stream) {
 
 template <int BT, int BW, int NS>
 hipError_t launch_z(const MxGemmArgs& a, hipStream_t stream) {
-    const int tiles = ((a.R + BT - 1) / BT) * ((a.C + BW - 1) / BW);
+    const int tiles = ((a.R + BT - 1) / BT) * ((a.cpad + BW - 1) / BW);
     // four steps' scales per 16-byte load where every scale row starts on 16 bytes
     if (scale_rows_16(a)) hipLaunchKernelGGL((gemm_mx_z_kernel<BT, BW, NS, 4>), dim3(tiles), dim3(256), 0, stream, a);
     else hipLaunchKernelGGL((gemm_mx_z_kernel<BT, BW, NS, 1>), dim3(tiles), dim3(256), 0, stream, a);
@@ -898,7 +898,7 @@ int mx_gemm_tile(int R, int C, int cus, int out_mx) {
         // the largest tile that still gives every CU a tile; else 128 x 192
         // tiles with three stages when they make one round on more than half
         // of the CUs; else the smallest
-        const long long t192 = (long long)((R + 127) / 128) * ((C + 191) / 192);
+        const long long t192 = (long long)((R + 127) / 128) * (((C + 127) / 128 * 128 + 191) / 192);
         if (t256 >= cus) return 0;
         if (t128 >= cus) return 1;
         if (2 * t192 > cus && t192 <= cus) return 3;
