@@ -17,14 +17,11 @@
 //   16x16x32 MFMAs) with the fragment reads of the next sub-step and the
 //   loads of step + 2 between them; persistent tiles, the next tile's first
 //   two steps loaded during the last two of the current one.
-// * The projection (MX-FP8 output, a few hundred tiles at most) runs a
-//   simpler kernel on v_mfma_scale_f32_16x16x128_f8f6f4 with tiles small
-//   enough to give every CU work: for the 4096 x 1536 projections 128 x 192
-//   tiles (256 of them) with three LDS stages, the loads of a step issued two
-//   steps ahead (measured on operands rotated through HBM: 38 against 41 us
-//   with 128 x 128 tiles on two stages and two workgroups per CU at depth
-//   4096, 110 against 131 us at depth 11008; the pipelined kernel's 256 x 128
-//   or 256 x 256 tiles on 192 or 96 CUs took 54-60 us at depth 4096).
+// * The projection (MX-FP8 output) runs a simpler kernel on
+//   v_mfma_scale_f32_16x16x128_f8f6f4: 128 x 128 tiles with two workgroups per
+//   CU, whose loads, LDS reads and MFMAs overlap with each other's, or 256 x 256
+//   tiles; or, on 128 x 192 tiles, the kernel of proj_mxfp8.hip.  The choice is
+//   mx_proj_tile's.
 //
 // v_mfma_scale_f32_32x32x64_f8f6f4 (operands "A" then "B"), as measured on
 // the device:
@@ -112,17 +109,18 @@ constexpr int MX_BK = 128;   // depth of one step: one block-scaled MFMA
 __device__ __forceinline__ int mx_swz(int r) { return (r >> 1) & 7; }
 
 // Tile BT tokens x BW output columns, 4 waves as 2 x 2, each BT/2 x BW/2,
-// NS LDS stages (the loads of step t + NS - 1 are issued at the start of
-// step t).  A stage holds the tile's BT + BW rows of 128 code bytes (token
+// two LDS stages (the loads of step t + 1 are issued at the start of step t).
+// A stage holds the tile's BT + BW rows of 128 code bytes (token
 // rows first).  The scale dwords (the 4 blocks of a step) of SS steps are
 // loaded together: SS = 1, one dword per row after the codes of each stage;
 // SS = 4 (scale rows 16-byte aligned), 16 bytes per row into one of two
 // areas after the stages, with the codes of every fourth step.  A scale load
 // gathers 64 rows, one memory line each, so a quarter of them as 16-byte
-// loads saves most of their cost (4096 x 1536 projections: 37.6 -> 36.7 us
-// at depth 4096, 107.7 -> 89.6 us at depth 11008).
-template <int BT, int BW, int NS, int SS>
+// loads saves most of their cost (4096 x 1536 projections on 128 x 192 tiles:
+// 107.7 -> 89.6 us at depth 11008).
+template <int BT, int BW, int SS>
 struct MxZCfg {
+    static constexpr int NS = 2;
     static constexpr int ROWS = BT + BW;
     static constexpr int DATA = ROWS * MX_BK;
     static constexpr int STAGE = SS == 1 ? DATA + ROWS * 4 : DATA;
@@ -134,14 +132,13 @@ struct MxZCfg {
     static constexpr int NSL = ROWS / 64;   // 256-byte scale loads per stage (64 rows each)
     static constexpr int LPD = NDL / 4;     // code loads per wave and stage
     static constexpr int LPS = (NSL + 3) / 4;   // scale loads per wave (uniform: extra ones repeat a load)
-    static constexpr int LPW = LPD + LPS;
     static_assert(BT % 64 == 0 && BW % 64 == 0 && NDL % 4 == 0, "tile");
-    static_assert((NS == 2 || NS == 3) && (NS - 2) * LPW < 64 && SMEM <= 160 * 1024, "stages");
+    static_assert(SMEM <= 160 * 1024, "stages");
     static_assert(SS == 1 || SS == 4, "scale steps");
     // whether step t's loads include scales, and where step t's scale bytes are
     static __device__ __forceinline__ bool scales_with(int t) { return SS == 1 || (t & 3) == 0; }
     static __device__ __forceinline__ int scale_area(int t) {
-        return SS == 1 ? (t % NS) * STAGE + DATA : NS * STAGE + ((t >> 2) & 1) * SAREA;
+        return SS == 1 ? (t & 1) * STAGE + DATA : NS * STAGE + ((t >> 2) & 1) * SAREA;
     }
 };
 
@@ -156,11 +153,11 @@ __device__ __forceinline__ void mx_barrier() { asm volatile("s_waitcnt lgkmcnt(0
 // bytes per lane).  Rows past the matrix read its last row (their results
 // are never stored); the 16-byte scale loads of a last group may read past
 // the matrix's steps (bytes never used; past the buffer they read zeros).
-template <int BT, int BW, int NS, int SS>
+template <int BT, int BW, int SS>
 __device__ __forceinline__ void mx_issue(unsigned char* smem, const MxGemmArgs& a, int row0, int col0, int t,
                                          int wave, int lane) {
-    using C = MxZCfg<BT, BW, NS, SS>;
-    unsigned char* stage = smem + (t % NS) * C::STAGE;
+    using C = MxZCfg<BT, BW, SS>;
+    unsigned char* stage = smem + (t & 1) * C::STAGE;
     const auto tr = __builtin_amdgcn_make_buffer_rsrc((void*)a.T, (short)0, (int)(a.R * a.ldt), 0x00020000);
     const auto wr = __builtin_amdgcn_make_buffer_rsrc((void*)a.W, (short)0, (int)(a.C * a.ldw), 0x00020000);
     const auto ts = __builtin_amdgcn_make_buffer_rsrc((void*)a.Ts, (short)0, (int)(a.R * a.ldts), 0x00020000);
@@ -209,10 +206,10 @@ __device__ __forceinline__ i32x8_t mx_frag(const unsigned char* stage, int rr, i
 
 // Tile BT tokens x BW columns, MX-FP8 output along the columns (codes and
 // one scale byte per 32 columns, up to cpad columns); one workgroup per tile.
-template <int BT, int BW, int NS, int SS>
+template <int BT, int BW, int SS>
 __global__ __launch_bounds__(256, (BT + BW) <= 256 ? 2 : 1)
 void gemm_mx_z_kernel(MxGemmArgs a) {
-    using C = MxZCfg<BT, BW, NS, SS>;
+    using C = MxZCfg<BT, BW, SS>;
     __shared__ __attribute__((aligned(1024))) unsigned char smem[C::SMEM];
 
     const int tiles_c = (a.cpad + BW - 1) / BW;   // the padding columns are written too
@@ -233,22 +230,16 @@ void gemm_mx_z_kernel(MxGemmArgs a) {
         for (int j = 0; j < C::NJ; ++j) acc[i][j] = f32x4_t{0.f, 0.f, 0.f, 0.f};
 
     const int steps = (a.D + MX_BK - 1) / MX_BK;
-    for (int t = 0; t < NS - 1 && t < steps; ++t) mx_issue<BT, BW, NS, SS>(smem, a, row0, col0, t, wave, lane);
+    mx_issue<BT, BW, SS>(smem, a, row0, col0, 0, wave, lane);
     for (int t = 0; t < steps; ++t) {
-        // this wave's loads of step t have landed (those of the newer steps
-        // may stay in flight); after the barrier every wave's have, and
-        // every wave is done with step t - 1, whose stage receives step
-        // t + NS - 1 (and whose scale area, with four-step groups, is not
-        // rewritten before step t + 4)
-        if (NS == 3 && t + 1 < steps) {
-            if (C::scales_with(t + 1)) v3_wait_vm<C::LPW>();
-            else v3_wait_vm<C::LPD>();
-        } else {
-            v3_wait_vm<0>();
-        }
+        // this wave's loads of step t have landed; after the barrier every
+        // wave's have, and every wave is done with step t - 1, whose stage
+        // receives step t + 1 (and whose scale area, with four-step groups, is
+        // not rewritten before step t + 4)
+        v3_wait_vm<0>();
         mx_barrier();
-        if (t + NS - 1 < steps) mx_issue<BT, BW, NS, SS>(smem, a, row0, col0, t + NS - 1, wave, lane);
-        const unsigned char* cur = smem + (t % NS) * C::STAGE;
+        if (t + 1 < steps) mx_issue<BT, BW, SS>(smem, a, row0, col0, t + 1, wave, lane);
+        const unsigned char* cur = smem + (t & 1) * C::STAGE;
         const unsigned char* sc = smem + C::scale_area(t) + (SS == 1 ? 0 : 4 * (t & 3));
         i32x8_t tf[C::NI];
         int tsc[C::NI];
@@ -880,62 +871,69 @@ hipError_t launch_pipelined(const MxGemmArgs& a, int cus, hipStream_t stream) {
     return hipGetLastError();
 }
 
-template <int BT, int BW, int NS>
+template <int BT, int BW>
 hipError_t launch_z(const MxGemmArgs& a, hipStream_t stream) {
     const int tiles = ((a.R + BT - 1) / BT) * ((a.cpad + BW - 1) / BW);
     // four steps' scales per 16-byte load where every scale row starts on 16 bytes
-    if (scale_rows_16(a)) hipLaunchKernelGGL((gemm_mx_z_kernel<BT, BW, NS, 4>), dim3(tiles), dim3(256), 0, stream, a);
-    else hipLaunchKernelGGL((gemm_mx_z_kernel<BT, BW, NS, 1>), dim3(tiles), dim3(256), 0, stream, a);
+    if (scale_rows_16(a)) hipLaunchKernelGGL((gemm_mx_z_kernel<BT, BW, 4>), dim3(tiles), dim3(256), 0, stream, a);
+    else hipLaunchKernelGGL((gemm_mx_z_kernel<BT, BW, 1>), dim3(tiles), dim3(256), 0, stream, a);
     return hipGetLastError();
 }
 
 }  // namespace
 
-int mx_gemm_tile(int R, int C, int cus, int out_mx) {
+// The projection's tile, by estimated time (us; fitted to the times of the
+// three over 17 sizes, operands rotated through HBM; it picks the fastest, or
+// one within 5%, at each).  A round of the chip costs, per 128-deep step: 256 x 256 tiles
+// 2.0, 128 x 192 ones (proj_mxfp8.hip) 0.85, 128 x 128 ones 1.06 with two
+// workgroups on every CU and 0.75 with one on each.  Measured, us:
+//    tokens x rows x depth     256 x 256   256 x 128   128 x 128   128 x 192
+//    4096 x 1536 x 11008          189         124          98          82
+//    8192 x 1536 x 11008          190         227         168         157
+//    8192 x 2458 x 24576          788         697         549         639
+//    8192 x 3072 x  4096          147         136         118         127
+//    5000 x 3000 x  6144          113         128         109         127
+//    8192 x 4096 x  8192          270         323         285         330
+//    2048 x 1536 x  4096           75          46          32          33
+// (256 x 128 tiles, one workgroup per CU: nowhere the fastest, gone.)
+MxProjTile mx_proj_tile(int R, int C, int D, int cus, double* us) {
+    const int steps = (D + MX_BK - 1) / MX_BK, cpad = (C + 127) / 128 * 128;
+    auto tiles = [&](int bt, int bw) { return (long long)((R + bt - 1) / bt) * ((cpad + bw - 1) / bw); };
+    auto rounds = [&](long long t) { return (double)((t + cus - 1) / cus); };
+    const double big = rounds(tiles(256, 256)) * (8.0 + 2.0 * steps);
+    const double wide = rounds(tiles(128, 192)) * (7.0 + 0.85 * steps);
+    const long long t = tiles(128, 128);
+    const long long pairs = t / (2 * cus), rest = t % (2 * cus);
+    double small = 2.0 + pairs * (4.0 + 1.06 * steps);
+    if (rest) small += rest <= cus ? 3.0 + 0.75 * steps : 4.0 + 1.06 * steps;
+    *us = big < wide ? (big < small ? big : small) : (wide < small ? wide : small);
+    return *us == small ? MX_TILE_128x128 : (*us == wide ? MX_TILE_128x192 : MX_TILE_256x256);
+}
+
+// The expansion: 256 x 256 tiles when they give every CU a tile or when 256 x
+// 128 tiles (half the work each) need twice the rounds or more.
+static bool expand_wide(int R, int C, int cus) {
     const long long t256 = (long long)((R + 255) / 256) * ((C + 255) / 256);
     const long long t128 = (long long)((R + 255) / 256) * ((C + 127) / 128);
-    if (out_mx) {
-        // the largest tile that still gives every CU a tile; else 128 x 192
-        // tiles with three stages when they make one round on more than half
-        // of the CUs; else the smallest
-        const long long t192 = (long long)((R + 127) / 128) * (((C + 127) / 128 * 128 + 191) / 192);
-        if (t256 >= cus) return 0;
-        if (t128 >= cus) return 1;
-        if (2 * t192 > cus && t192 <= cus) return 3;
-        return 2;
-    }
-    // 256 x 256 tiles when they give every CU a tile or when 256 x 128 tiles
-    // (half the work each) need twice the rounds or more
     const long long r256 = (t256 + cus - 1) / cus, r128 = (t128 + cus - 1) / cus;
-    return (t256 >= cus || 2 * r256 <= r128) ? 0 : 1;
+    return t256 >= cus || 2 * r256 <= r128;
 }
 
 // Small tiles for up to about a thousand tokens where they are estimated
-// faster than the tiles above.  Those take, per 128-deep step: in the
-// projection 0.83 us on 128 x 128 tiles (two per CU; 24 us at 1536 rows x
-// 4096, 71 at 11008, whatever the tokens) and 1.1 us on 128 x 192 tiles; in
-// the expansion 0.85 to 1.25 us on 256 x 128 tiles as their token rows fill,
+// faster than the tiles above.  Those take, per 128-deep step, in the
+// expansion 0.85 to 1.25 us on 256 x 128 tiles as their token rows fill,
 // 1.8 us on 256 x 256 (22016 x 1536: 14 us at 8 tokens, 20 at 200, small tiles
 // 10 and 41).
 int mx_small_config(int R, int C, int D, int cus, int out_mx) {
     const int steps = (D + MX_BK - 1) / MX_BK;
-    auto rounds = [&](int bm, int bn, int slots) {
+    auto rounds = [&](int bm, int bn) {
         const long long t = (long long)((R + bm - 1) / bm) * ((C + bn - 1) / bn);
-        return (double)((t + slots - 1) / slots);
+        return (double)((t + cus - 1) / cus);
     };
     double us;
-    switch (mx_gemm_tile(R, C, cus, out_mx)) {
-        case 0:
-            if (out_mx) return -1;
-            us = 3.0 + 1.8 * steps * rounds(256, 256, cus);
-            break;
-        case 1:
-            if (out_mx) return -1;
-            us = 3.0 + (0.85 + 0.4 * (R < 256 ? R : 256) / 256.0) * steps * rounds(256, 128, cus);
-            break;
-        case 3: us = 3.0 + 1.1 * steps; break;
-        default: us = 1.5 + 0.83 * steps * rounds(128, 128, 2 * cus); break;
-    }
+    if (out_mx) mx_proj_tile(R, C, D, cus, &us);
+    else if (expand_wide(R, C, cus)) us = 3.0 + 1.8 * steps * rounds(256, 256);
+    else us = 3.0 + (0.85 + 0.4 * (R < 256 ? R : 256) / 256.0) * steps * rounds(256, 128);
     return mx_mid_config(R, C, D, cus, out_mx, us);
 }
 
@@ -953,16 +951,15 @@ hipError_t launch_gemm_mx(const MxGemmArgs& a, int out_mx, int cus, hipStream_t 
         const int config = mx_small_config(a.R, a.C, a.D, cus, out_mx);
         if (config >= 0) return launch_mx_mid(a, out_mx, config, scale_rows_16(a), stream);
     }
-    const int tile = mx_gemm_tile(a.R, a.C, cus, out_mx);
     if (out_mx) {
-        switch (tile) {
-            case 0: return launch_z<256, 256, 2>(a, stream);
-            case 1: return launch_z<256, 128, 2>(a, stream);
-            case 3: return launch_z<128, 192, 3>(a, stream);
-            default: return launch_z<128, 128, 2>(a, stream);
+        double us;
+        switch (mx_proj_tile(a.R, a.C, a.D, cus, &us)) {
+            case MX_TILE_256x256: return launch_z<256, 256>(a, stream);
+            case MX_TILE_128x192: return launch_proj_mx(a, scale_rows_16(a), stream);
+            default: return launch_z<128, 128>(a, stream);
         }
     }
-    return tile == 0 ? launch_pipelined<256>(a, cus, stream) : launch_pipelined<128>(a, cus, stream);
+    return expand_wide(a.R, a.C, cus) ? launch_pipelined<256>(a, cus, stream) : launch_pipelined<128>(a, cus, stream);
 }
 
 hipError_t launch_mx_quantize(const uint16_t* A, int64_t lda, int R, int C, uint8_t* Q, int64_t ldq, uint8_t* S,

@@ -159,9 +159,9 @@ struct MxGemmArgs {
     int t_pairs = 0;                    // the token codes T (bf16 output only)
     int out_pairs = 0;                  // the MX-FP8 output codes
 };
-// Tile of the MX GEMM for R x C outputs (0: 256 x 256, 1: 256 x 128, 2: 128 x 128;
-// 2 only for MX-FP8 output).
-int mx_gemm_tile(int R, int C, int cus, int out_mx);
+// The projection's tile for R x C outputs at depth D, and its estimated time.
+enum MxProjTile { MX_TILE_256x256, MX_TILE_128x128, MX_TILE_128x192 };
+MxProjTile mx_proj_tile(int R, int C, int D, int cus, double* us);
 // out_mx: write MX-FP8 (codes and scales along the columns) instead of bf16.
 // hipErrorInvalidValue when an operand spans 2^31 bytes or more.
 hipError_t launch_gemm_mx(const MxGemmArgs& a, int out_mx, int cus, hipStream_t stream);
@@ -172,6 +172,8 @@ int mx_small_config(int R, int C, int D, int cus, int out_mx);
 // estimated below tiled_us; its launch.
 int mx_mid_config(int R, int C, int D, int cus, int out_mx, double tiled_us);
 hipError_t launch_mx_mid(const MxGemmArgs& a, int out_mx, int config, bool scales16, hipStream_t stream);
+// proj_mxfp8.hip: MX-FP8 output on 128 x 192 tiles whose waves halve every step.
+hipError_t launch_proj_mx(const MxGemmArgs& a, bool scales16, hipStream_t stream);
 hipError_t launch_mx_quantize(const uint16_t* A, int64_t lda, int R, int C, uint8_t* Q, int64_t ldq, uint8_t* S,
                               int64_t lds, hipStream_t stream);
 

@@ -29,4 +29,22 @@ __device__ __forceinline__ int mx_scale_byte(float amax) {
     return b < 0 ? 0 : (b > 254 ? 254 : b);
 }
 
+// The order in which a workgroup walks the depth steps: each XCD starts an
+// eighth of the whole groups of four steps further on (groups, so that the
+// steps that share a scale load stay together; a last partial group keeps its
+// place), so that the XCDs read different columns of the operands at a time
+// (measured in proj_mxfp8.hip).
+struct MxDepthOrder {
+    int whole, rot;
+    __device__ __forceinline__ explicit MxDepthOrder(int steps) {
+        whole = steps & ~3;
+        rot = (int)(blockIdx.x & 7) * (steps >> 2) / 8 * 4;
+    }
+    __device__ __forceinline__ int operator()(int t) const {
+        if (t >= whole) return t;
+        const int r = t + rot;
+        return r >= whole ? r - whole : r;
+    }
+};
+
 }  // namespace espace

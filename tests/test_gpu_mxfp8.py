@@ -212,8 +212,8 @@ def test_mxfp8_llama2_7b_qkv_sampled(E):
 # (N, L, K) of projections whose operands' scale rows are laid out twice: at
 # the smallest leading dimension (not a multiple of 16 bytes: one scale
 # dword per row and step) and padded to 16 bytes as the library allocates
-# them (four steps' scales per 16-byte load), on 128 x 192 tiles with three stages (6 steps: a last group
-# of two), 128 x 128 tiles with two stages, and 256 x 256 tiles (33 steps).
+# them (four steps' scales per 16-byte load), on 128 x 128 tiles (6 steps: a last group
+# of two; one and several tiles per CU) and 256 x 256 tiles (33 steps).
 SCALE_LAYOUTS = [(5000, 700, 700), (1000, 300, 700), (4096, 4096, 4100)]
 
 
