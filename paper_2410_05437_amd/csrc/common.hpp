@@ -91,11 +91,17 @@ __device__ __forceinline__ int xcd_contiguous(int bid, int nblocks) {
 // The order in which a workgroup walks the full depth steps first .. last - 1:
 // each XCD starts an eighth of them further on (a step past them keeps its
 // place), so that the XCDs read different columns of the operands at a time
-// instead of all the same ones.  Measured on operands rotated through HBM: the
-// 128 x 192 tiles of 4096 x 1536 x 11008 143.5 -> 136.2 us (their loads alone
-// 137 -> 124), 256 x 256 tiles of 4096 x 12288 x 4096 321 -> 305, of 8192 x 2458 x
-// 24576 987 -> 922, of 4096 x 12288 x 1536 no change.  The workgroups of an XCD,
+// instead of all the same ones.  Measured on operands rotated through HBM, us with
+// one order -> with an order per XCD: 128 x 192 tiles of 4096 x 1536 x 11008 149 ->
+// 134, 256 x 256 tiles of 4096 x 12288 x 4096 316 -> 295, 256 x 192 ones of 8192 x
+// 2458 x 24576 1062 -> 993, 256 x 160 ones 875 -> 830.  Over 168 sizes (32 to 900 MB of
+// operands): 128 x 192 tiles 2% faster, 256 x 192 2%, 256 x 160 level (more than 5%
+// either way at single sizes); 192 x 192 1% slower, so they keep one order.  256 x
+// 256 and 128 x 128 tiles: one_depth_order (kernels.hpp).  The workgroups of an XCD,
 // which share operand panels in its L2, keep the same order.
+//
+// A row's sums are added in the order of the XCD its tile falls to, so equal rows of
+// one call may differ in the last bits; the same call gives the same bits again.
 struct DepthOrder {
     int first, last, rot;
     __device__ __forceinline__ DepthOrder(int f, int l) : first(f), last(l) {

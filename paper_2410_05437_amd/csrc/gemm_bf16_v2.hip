@@ -310,7 +310,7 @@ void gemm_tn_bf16_v2_kernel(const uint16_t* __restrict__ A, int64_t lda,
     int kt_end = kt0 + ktiles_per_split;
     kt_end = kt_end < ktiles ? kt_end : ktiles;
 
-    const DepthOrder order(kt0, D / BK < kt_end ? D / BK : kt_end);
+    const DepthOrder order(kt0, (map & MAP_ONE_ORDER) ? kt0 : (D / BK < kt_end ? D / BK : kt_end));
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -484,12 +484,13 @@ hipError_t launch_v2(const GemmArgs& g, hipStream_t stream) {
     const int ktiles = (g.D + BK - 1) / BK;
     const int S = g.splits;
     const int ktps = (ktiles + S - 1) / S;
+    const int map = one_depth_order(g, BM, BN) ? MAP_ONE_ORDER : 0;
     dim3 grid(tiles_r * tiles_c, S);
     dim3 block(WM * WN * 64);
     if (S == 1) {
         hipLaunchKernelGGL((gemm_tn_bf16_v2_kernel<BM, BN, WM, WN, BK, STAGES, MODE_BF16, MI>), grid, block,
                            0, stream, g.A, g.lda, g.B, g.ldb, g.C, g.ldc, g.R, g.Cc, g.D, tiles_c,
-                           ktps, (int64_t)0, 0, nullptr, nullptr, 0ull, g.wait, g.c_pairs);
+                           ktps, (int64_t)0, map, nullptr, nullptr, 0ull, g.wait, g.c_pairs);
         return hipGetLastError();
     }
     if (S == 2 && g.pair) {
@@ -500,14 +501,14 @@ hipError_t launch_v2(const GemmArgs& g, hipStream_t stream) {
             reinterpret_cast<unsigned long long*>(g.partial + (size_t)ntiles * BM * BN);
         hipLaunchKernelGGL((gemm_tn_bf16_v2_kernel<BM, BN, WM, WN, BK, STAGES, MODE_PAIR, MI>), grid, block,
                            0, stream, g.A, g.lda, g.B, g.ldb, g.C, g.ldc, g.R, g.Cc, g.D, tiles_c,
-                           ktps, (int64_t)0, 0, state, g.partial, g.epoch, g.wait, g.c_pairs);
+                           ktps, (int64_t)0, map, state, g.partial, g.epoch, g.wait, g.c_pairs);
         return hipGetLastError();
     }
     const int64_t ldp = splitk_ld(g.Cc);
     const int64_t split_stride = (int64_t)g.R * ldp;
     hipLaunchKernelGGL((gemm_tn_bf16_v2_kernel<BM, BN, WM, WN, BK, STAGES, MODE_F32, MI>), grid, block, 0,
                        stream, g.A, g.lda, g.B, g.ldb, (void*)g.partial, ldp, g.R, g.Cc, g.D,
-                       tiles_c, ktps, split_stride, 0, nullptr, nullptr, 0ull, g.wait, 0);
+                       tiles_c, ktps, split_stride, map, nullptr, nullptr, 0ull, g.wait, 0);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     return launch_splitk_reduce(g.partial, S, split_stride, ldp, g.C, g.ldc, g.R, g.Cc,

@@ -72,9 +72,9 @@ void gemm_tn_bf16_v3_kernel(const uint16_t* __restrict__ A, int64_t lda,
     // the next item's first two steps can be loaded ahead
     const bool ahead_ok = MODE == V3_BF16 && (Cc & 7) == 0 && kt0 + 2 <= nfull;
 
-    // (not in the symmetric product, where most panels are shared by many XCDs:
-    // K = 4096, 8192 tokens 140 -> 157 us)
-    const DepthOrder order(kt0, (map & 8) ? kt0 : nfull);
+    // (one order in the symmetric product, where most panels are shared by many
+    // XCDs: K = 4096, 8192 tokens 140 us, with an order per XCD 157)
+    const DepthOrder order(kt0, (map & (8 | MAP_ONE_ORDER)) ? kt0 : nfull);
 
     const int lane = threadIdx.x & 63;
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -389,7 +389,7 @@ hipError_t launch_v3(const GemmArgs& g, hipStream_t stream) {
     const bool pair = g.pair && S == 2 && (ktiles + ktps - 1) / ktps == 2;
     S = (ktiles + ktps - 1) / ktps;                 // no empty depth range
     dim3 block(V3_NW * 64);
-    const int map = 0;
+    const int map = one_depth_order(g, V3_BM, BN) ? MAP_ONE_ORDER : 0;
     if (S == 1) {
         // one workgroup per CU, each taking every cus-th tile
         const int persistent = g.cus > 0 ? g.cus : 256;

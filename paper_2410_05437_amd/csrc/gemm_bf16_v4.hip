@@ -92,7 +92,7 @@ void gemm_tn_bf16_v4_kernel(const uint16_t* __restrict__ A, int64_t lda, const u
     const int ktiles = (D + DK - 1) / DK;
     const int kt0 = blockIdx.y * sps;
     const int kt_end = min(kt0 + sps, ktiles);
-    const DepthOrder order(kt0, kt_end);
+    const DepthOrder order(kt0, BM == 192 ? kt0 : kt_end);
     // loads of step kt into stage st; past the range they still are issued, from
     // past the buffers, so that the count in flight is the same throughout;
     // chunks past the depth are zeros, the one that straddles it is masked

@@ -56,6 +56,20 @@ struct GemmArgs {
     int c_pairs = 0;    // write C (bf16) in the row-pair layout (ldc its pair pitch)
 };
 
+// Whether all XCDs walk the depth of a tiled product in one order (DepthOrder of
+// common.hpp gives each its own start).  256 x 256 and 128 x 128 tiles from 320 MB of
+// operands or 16384 of depth on: past the 256 MB Infinity Cache a panel that several
+// XCDs read is found there only if they read it at about the same time.  Over 44 such
+// sizes an order per XCD cost 256 x 256 tiles 1.3% (1180 x 22272 x 20168: 1394 -> 1528
+// us, 6144 x 2458 x 24576: 597 -> 610), 128 x 128 ones 2.8%; over the 124 others it saved
+// 2.3 and 2.0%.
+inline bool one_depth_order(const GemmArgs& g, int bm, int bn) {
+    return bm == bn && (((int64_t)g.R + g.Cc) * g.D >= 160000000 || g.D >= 16384);
+}
+
+// Bits of the tiled kernels' `map` argument next to those of tile_coords
+constexpr int MAP_ONE_ORDER = 16;                 // one depth order for all XCDs
+
 // offset (elements) of element (r, k) of a row-pair matrix with pair pitch ld
 __host__ __device__ inline int64_t pair_offset(int64_t r, int64_t k, int64_t ld) {
     return (r >> 1) * ld + (k >> 5) * 64 + (r & 1) * 32 + (k & 31);

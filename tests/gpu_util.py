@@ -1,6 +1,8 @@
 """Helpers for the GPU tests: move seeded inputs to the device with padded
 rows whose padding holds NaN (so any use of padding shows up), and bring
 outputs back as float64."""
+import re
+
 import numpy as np
 import pytest
 import torch
@@ -52,3 +54,24 @@ def padding(t):
     ld = t.stride(0)
     base = t.as_strided((R, ld), (ld, 1))
     return base[:, C:].float().cpu().numpy()
+
+
+TILES = {0: "256x256", 1: "256x128", 2: "128x256", 3: "128x128", 4: "256x256", 5: "256x256", 6: "128x192",
+         7: "256x192", 8: "192x192", 9: "256x160"}
+
+
+def plans(capfd, call):
+    """(call(), the plans of the bfloat16 products it ran): one dict each, with the
+    sizes R, Cc, D, the kind of kernel, the tile's name (tiled) or index (small
+    tiles), the depth ranges (splits), whether two are combined inside the kernel
+    (pair), and rows1, tile2, ... of a second launch by rows."""
+    capfd.readouterr()
+    out = call()
+    got = []
+    for line in re.findall(r"^espace plan (.*)$", capfd.readouterr().err, re.M):
+        p = {k: int(v) for k, v in re.findall(r"(\w+)=(\d+)", line)}
+        p["kind"] = {0: "tiled", 1: "small", 3: "gemv", 4: "stream"}[p["kind"]]
+        if p["kind"] == "tiled":
+            p["tile"], p["tile2"] = TILES[p["tile"]], TILES[p["tile2"]]
+        got.append(p)
+    return out, got
