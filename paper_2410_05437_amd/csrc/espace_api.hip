@@ -131,8 +131,6 @@ struct Plan {
 
 int ceil_div(int64_t a, int64_t b) { return (int)((a + b - 1) / b); }
 
-struct TileShape { int tile, bm, bn, per_cu; double eff; };
-
 // Per-call tags of the state words in workspaces (decode counters, pair
 // states): a counter started from a random 64-bit value, so that leftover
 // workspace contents match a tag with negligible probability.
@@ -158,26 +156,48 @@ void set_partial_bytes(Plan& p, int64_t R, int64_t Cc) {
     }
 }
 
+// A tiled product's price: per round of workgroups its ramp and write-out, and the
+// tile's area times its depth over a relative rate.
+//  * A last round that leaves CUs idle runs faster, by up to 0.29; 128 x 128 tiles
+//    with one workgroup instead of two on a CU by more.
+//  * Rows that do not start on cache lines (128 bytes) cost each tile `off_line` of
+//    its time, half lines a third of that: a step's 128 bytes of a row are two lines.
+//  * A pair's second half waits for the first's stores, on 256 x 192 tiles for longest
+//    where all run at once.
+//  * The operands come from HBM at 5.15 TB/s, all but hidden where they take less.
+// Fitted to 16280 measured times (638 sizes of 3 to 12288 rows, 200 to 24576 columns
+// and 300 to 24576 of depth; every tile, 1 to 4 depth ranges, pairs, and the small
+// tiles; operands rotated through HBM), 4.75 us and 24.85e-6 us a unit: within 8% of the
+// times (rms), and the cheapest plan takes 1.2% more on average than the best of
+// them.  The rates before were fitted to a dozen sizes: 4.7% more, and at some sizes
+// up to 20% more than with the tiles there were before 192 x 192 and 256 x 160.
+constexpr double kUnitUs = 24.85e-6;
+struct TileShape { int tile, bm, bn, per_cu; double rate, off_line, round; };
+
 Plan plan_tiled_one(int R, int Cc, int D, int cus, double* cost_out) {
     // Estimated time of each tile shape (and depth split) from the number of
-    // rounds of workgroups the chip needs, the per-tile work and a relative
-    // efficiency of the tile shape; the cheapest wins.  Two depth halves can
-    // also be combined inside the kernel ("pair"), which costs one fp32 tile
+    // rounds of workgroups the chip needs; the cheapest wins.  Two depth halves
+    // can also be combined inside the kernel ("pair"), which costs one fp32 tile
     // written and read per output tile instead of a reduction pass.
     static const TileShape shapes[] = {
-        {espace::TILE_256x256_W8T, 256, 256, 1, 1.00},
-        {espace::TILE_256x192_W8, 256, 192, 1, 0.97},
-        {espace::TILE_256x128, 256, 128, 1, 0.85},
-        {espace::TILE_128x256, 128, 256, 1, 0.85},
-        {espace::TILE_128x128, 128, 128, 2, 0.70},
-        {espace::TILE_128x192, 128, 192, 1, 0.70},
-        {espace::TILE_192x192, 192, 192, 1, 0.95},
-        // three rounds of it against two of 256 x 256: 8192 x 3686 x 24576, in the
-        // layer 1632 against 1506 us
-        {espace::TILE_256x160, 256, 160, 1, 0.91},
+        {espace::TILE_256x256_W8T, 256, 256, 1, 1.000, 0.331, 101e3},
+        {espace::TILE_256x192_W8, 256, 192, 1, 0.933, 0.355, 101e3},
+        {espace::TILE_256x128, 256, 128, 1, 0.727, 0.205, 101e3},
+        {espace::TILE_128x256, 128, 256, 1, 0.701, 0.233, 101e3},
+        {espace::TILE_128x128, 128, 128, 2, 0.800, 0.255, 40e3},
+        {espace::TILE_128x192, 128, 192, 1, 0.778, 0.242, 60e3},
+        {espace::TILE_192x192, 192, 192, 1, 0.905, 0.203, 217e3},
+        {espace::TILE_256x160, 256, 160, 1, 0.889, 0.158, 233e3},
     };
+    // 128 x 192 at long depths (gemm_bf16_v4.hip); past the Infinity Cache (256 MB
+    // of operands) its re-reads slow it more than the other shapes
+    const bool past_cache = ((int64_t)R + Cc) * D >= 128000000;
+    const TileShape halved{espace::TILE_128x192, 128, 192, 1, past_cache ? 0.817 : 0.845, past_cache ? 0.41 : 0.325, 212e3};
+    const int64_t row_bytes = round_up(D, 8) * 2;
+    const double off_line = row_bytes % 128 == 0 ? 0.0 : (row_bytes % 64 == 0 ? 0.33 : 1.0);
     const int ktiles = ceil_div(D, 64);
     const double byte_cost = 315.0 / (2.0 * 64 * cus);   // bytes priced against the MFMA rate
+    const double hbm = 2e-6 * ((double)R + Cc) * D / 5.15 / kUnitUs;
     Plan best;
     best.kind = KIND_TILED;
     double best_cost = 1e300;
@@ -189,20 +209,23 @@ Plan plan_tiled_one(int R, int Cc, int D, int cus, double* cost_out) {
             const bool halving = s.tile == espace::TILE_192x192 || s.tile == espace::TILE_256x160;
             for (int pair = 0; pair <= (splits == 2 && !halving ? 1 : 0); ++pair) {
                 const int64_t blocks = tiles * splits;
-                const int64_t rounds = (blocks + slots - 1) / slots;
+                const int64_t full = blocks / slots, rest = blocks % slots;
+                const bool deep = s.tile == espace::TILE_128x192 && !pair &&
+                                  ceil_div(ktiles, splits) >= espace::V4_MIN_STEPS;
+                const TileShape& t = deep ? halved : s;
                 // a round runs per_cu blocks on every CU
-                const double per_round = (double)s.bm * s.bn * ceil_div(ktiles, splits) * s.per_cu;
-                double cost = rounds * per_round / s.eff;
-                // 128 x 192 tiles at long depths (gemm_bf16_v4.hip): a better
-                // rate and 6 µs of ramp and write-out per round (4096 x 1536:
-                // 55 µs at depth 4096, 131 at 11008; 12288 rows: 160)
-                if (s.tile == espace::TILE_128x192 && !pair && ceil_div(ktiles, splits) >= espace::V4_MIN_STEPS)
-                    cost = rounds * (per_round / 0.90 + 220e3);
-                if (halving) cost += rounds * 220e3;
-                // the pair hand-off prices at 1.6x its bytes (measured: the
-                // second half waits for the first's stores)
-                if (pair) cost += 3.2 * tiles * s.bm * s.bn * 4.0 * byte_cost;
-                else if (splits > 1) cost += 2.0 * splits * (double)R * Cc * 4.0 * byte_cost;
+                const double work = (double)s.bm * s.bn * ceil_div(ktiles, splits) * s.per_cu / t.rate *
+                                    (1.0 + t.off_line * off_line);
+                double cost = full * (work + t.round);
+                const double fill = (double)rest / slots;
+                if (rest)
+                    cost += work * (s.per_cu == 2 && fill < 0.5 ? 0.55 + 0.612 * fill : 0.712 + 0.288 * fill) + t.round;
+                if (pair)
+                    cost += 57e3 + 1.48 * tiles * s.bm * s.bn * 4.0 * byte_cost +
+                            (blocks <= slots && s.tile == espace::TILE_256x192_W8 ? 0.122 * work : 0.0);
+                else if (splits > 1)
+                    cost += 97e3 + 1.37 * splits * (double)R * Cc * 4.0 * byte_cost;
+                cost = std::max(cost, hbm) + 0.16 * std::min(cost, hbm);
                 if (cost < best_cost) {
                     best_cost = cost;
                     best.tile = s.tile;
@@ -220,16 +243,14 @@ Plan plan_tiled_one(int R, int Cc, int D, int cus, double* cost_out) {
 Plan plan_tiled(int R, int Cc, int D, int cus, double* cost_out) {
     // A product whose tiles leave the last round of workgroups partly empty
     // can run as two launches split by rows, each with whole rounds.  Taken
-    // when the model prices it at least 3% cheaper, a launch counted as 3 µs
-    // (110 000 of its units at the expand GEMM's measured rate).  Measured
-    // (operands rotated through HBM): the Llama2-7B FFN up+gate fold, 22016 x
-    // 1536 at depth 4096, 271 -> 247 µs; the GPT3-22B FFN up projection at
-    // L = 2458, 8192 x 2458 at depth 6144, 258 -> 240 µs, and the down one,
-    // depth 24576, 1039 -> 1027 µs; the up+gate dense product (4096 x 22016 x
-    // 4096) 593 -> 597 µs, within the noise; the QKV fold,
-    // 12288 x 1536 (1.5 rounds of 256 x 192 tiles, split as 4096 rows on 128 x
-    // 192 tiles and 8192 on 256 x 192), 162 -> 167 µs, no gain: a half-empty
-    // last round runs at higher clocks than the model assumes.
+    // when the model prices it at least 3% cheaper, a launch counted as 2.7 µs
+    // (110 000 of its units).  Measured (operands rotated through HBM): the
+    // GPT3-22B FFN down projection at L = 2458, 8192 x 2458 at depth 24576, 905 µs
+    // in one launch of 256 x 160 tiles, 805 as 1792 rows in three depth ranges and
+    // 6400 rows in one round of 256 x 256 tiles; the Llama2-7B FFN up+gate fold,
+    // 22016 x 1536 at depth 4096, 272 µs on 256 x 256 tiles, 235 as 256 rows in four
+    // ranges and the rest in two rounds.  The QKV fold, 12288 x 1536 x 4096, fits two
+    // rounds of 192 x 192 tiles: 142 µs against 149 split by rows.
     double cost = 0;
     Plan best = plan_tiled_one(R, Cc, D, cus, &cost);
     *cost_out = cost;
@@ -305,13 +326,13 @@ Plan plan_bf16(int R, int Cc, int D) {
     double cost = 0;
     const Plan t = plan_tiled(R, Cc, D, cus, &cost);
     if (R > kMidMaxTokens) return t;
-    // the tiled plan's price in µs: its units at the expand GEMM's rate, a
-    // launch and its ramp, and the reduction launch of a depth split (fitted
-    // to the same measurements as mid_plan's; 333 x 12288 x 1536 stays tiled,
-    // 23 against 34 µs, 128 x 12288 x 1536 does not, 21 against 15)
-    const double tiled_us = 5.0 + 0.95 * 27.3e-6 * cost + (t.splits > 1 ? 2.5 : 0.0);
+    // the tiled plan's price in µs: its units, a launch and its ramp
+    const double tiled_us = 4.75 + kUnitUs * cost;
     const Plan m = plan_mid(R, Cc, D, cus, &us);
-    return us < tiled_us ? m : t;
+    // from 33 tokens on the small tiles' price is 5% high on average, at shallow
+    // depths 6% low (64 x 24576 x 1966: 28.0 against 34.1 us, both priced 30.7; 282 x 7701
+    // x 384: 12.2 against 9.0)
+    return us * (D < 1024 ? 1.06 : 0.95) < tiled_us ? m : t;
 }
 
 // A product's plan depends on its sizes and the device's CUs alone; each

@@ -45,6 +45,7 @@
 // Depth tail: 16-byte chunks at or past D are loaded from past the buffer
 // (zeros); the chunk that straddles D is masked in registers, both operands.
 #include <algorithm>
+#include <cmath>
 
 #include "common.hpp"
 #include "kernels.hpp"
@@ -278,17 +279,20 @@ hipError_t launch_cfg_mid(const GemmArgs& g, bool upper, hipStream_t stream) {
 }  // namespace
 
 // Estimated time of a product (us) with the best of the tiles, from what
-// bounds it: B from HBM at 5.5 TB/s against the tiles' operand bytes through
-// each CU's load path at 75 KB/us, round by round; the two overlap except for
-// about 0.3 of the smaller.  A launch is 2.8 us, each further round 4 (the
-// rings drain and refill; one workgroup fits a CU), a depth split the
-// reduction launch and its traffic.  Fitted to 1800 measured times of these
-// tiles over 110 sizes (1 to 512 tokens); choosing by it costs 2% on average
-// against the best of them.
+// bounds it: B from HBM at 5.3 TB/s and the tiles' operand bytes through each
+// CU's load path at 74 KB/us, round by round, which overlap to the root of their
+// squares' sum.  Rows off the cache lines cost 25% of the one and 34% of the other,
+// half lines a third of that (a step's 128 bytes of a row are two lines),
+// half-filled operands 5% of the other.  A launch is 2.85 us, each further round 2.7
+// (the rings drain and refill; one workgroup fits a CU), a depth split the reduction
+// launch and its traffic.  Fitted with the tiled kernels' price (espace_api.hip), to
+// 2800 times of these tiles at 3 to 1024 tokens.
 double mid_plan(int R, int Cc, int D, int cus, int* config, int* splits) {
     double best = 1e300;
     const int steps = (D + MK - 1) / MK;
-    const double hbm = 2e-6 * Cc * D / 5.5;
+    const int64_t row_bytes = ((int64_t)D + 7) / 8 * 16;
+    const double off_line = row_bytes % 128 == 0 ? 0.0 : (row_bytes % 64 == 0 ? 0.33 : 1.0);
+    const double hbm = 2e-6 * Cc * D / 5.32 * (1.0 + 0.25 * off_line);
     for (int i = 0; i < kMidCount; ++i) {
         const int bm = kMid[i].bm, bn = kMid[i].bn;
         // half-filled operands serve only token counts that fit one tile
@@ -297,10 +301,15 @@ double mid_plan(int R, int Cc, int D, int cus, int* config, int* splits) {
         const int64_t tiles = (int64_t)((R + bm - 1) / bm) * ((Cc + bn - 1) / bn);
         for (int s = 1; s <= 4; ++s) {
             if (s > 1 && steps / s < 32) break;    // at least 4 to 8 steps per wave
+            // up to 16 tokens: only where the tiles leave most CUs idle (512 x 24576 at
+            // one token 14.2 -> 10.8 us with four ranges, but 6144 x 24576 54 -> 60, at 8
+            // tokens 57 -> 60)
+            if (s > 1 && R <= 16 && Cc > 10 * cus) break;
             const int64_t rounds = (tiles * s + cus - 1) / cus;
-            const double load = rounds * (bm + bn) * (double)((steps + s - 1) / s) * (MK * 2) / 75e3;
-            double t = 2.8 + std::max(hbm, load) + 0.3 * std::min(hbm, load) + 4.0 * (rounds - 1) + 0.0003 * bm * bn;
-            if (s > 1) t += 3.5 + 4e-6 * s * R * (double)Cc / 3.0;
+            const double load = rounds * (bm + bn) * (double)((steps + s - 1) / s) * (MK * 2) / 74e3 *
+                                (1.0 + 0.34 * off_line) * (bn == 8 ? 1.05 : 1.0);
+            double t = 2.85 + std::sqrt(hbm * hbm + load * load) + 2.7 * (rounds - 1) + 0.0004 * bm * bn;
+            if (s > 1) t += 3.4 + 1.3e-6 * s * R * (double)Cc;
             if (t < best) {
                 best = t;
                 *config = i;
