@@ -275,6 +275,14 @@ Plan plan_tiled(int R, int Cc, int D, int cus, double* cost_out) {
     return best;
 }
 
+// How rows of D bf16 elements, laid out as closely as the library takes them, lie on
+// the 128-byte cache lines: 0 on them, 1 on half lines, 2 on neither (a 128-byte piece
+// of a row is then two lines, for half lines every other row's).
+int off_lines(int64_t D) {
+    const int64_t bytes = round_up(D, 8) * 2;
+    return bytes % 128 == 0 ? 0 : (bytes % 64 == 0 ? 1 : 2);
+}
+
 // 3 to 16 tokens on more rows of B than one round of the small-tile kernel's
 // widest tiles holds: the persistent streaming kernel, which balances groups
 // of 16 rows over the CUs (28000 x 1536 at 16 tokens 17.8 against 19.8 µs,
@@ -285,17 +293,43 @@ bool use_stream(int R, int Cc, int D) {
     return R >= 3 && espace::stream_supported(R, D) && (int64_t)Cc > 96 * (int64_t)device_cus();
 }
 
-// One or two tokens: whole-row streaming with bf16 dot products (D ≤ 4096 for
-// the short rows' form, else tokens in LDS), unless the rows are few and
-// long, where the small tiles split the depth over a workgroup's waves.  At
-// one token 1536 x 11008 9.9 against 10.9 µs, 2458 x 6144 8.7 against 9.6, but
-// 12288 x 4096 and longer weights within 6% either way; at two tokens 2458 x
-// 24576 26.4 against 32.5, 12288 x 4096 17.5 against 20.0, 6144 x 2458 8.3
-// against 8.9, but 22016 x 1536 14.2 against 13.5.
+// One or two tokens: whole-row streaming with bf16 dot products (rows of up to 2048
+// elements in the short rows' form, else tokens in LDS), unless the small tiles, which
+// split the depth over a workgroup's waves, have a tile for about every CU.  Both
+// measured at 400 sizes; us, streaming / small tiles:
+//  * One token, rows on cache lines.  Tiles of 16 rows in one round, past the depths
+//    where the streaming kernel's 4 KB blocks come out even: 1536 x 11008 10.7 / 10.0,
+//    4096 x 24576 40.8 / 36.6, 3584 x 5120 10.9 / 9.7; but 1024 x 24576 14.0 / 15.7, 3072 x
+//    6144 10.4 / 10.8, 3072 x 8192 12.0 / 12.7.  Tiles of 32 rows (20 to 32 per CU) only
+//    where the tokens' LDS leaves the streaming kernel few workgroups per CU: 6144 x
+//    24576 57.7 / 54.1, 6144 x 13824 35.3 / 33.6; but 5120 x 8192 17.8 / 18.9, 6144 x 11008
+//    29.1 / 29.8.  Rows off the lines: never (4096 x 10000 18.7 / 18.1, 5120 x 10000 22.2 /
+//    28.9).
+//  * Two tokens, depths past 4096.  Up to 48 rows per CU (4096 x 11008 25.4 / 18.6,
+//    12288 x 16384 84 / 76), 64 at 8192 to 16384 of depth (16384 x 13824 105 / 84, but
+//    16384 x 8192 49.9 / 52.2 and x 16384 106 / 114); few rows at 6144 to 8192 stay (512 x
+//    8192 6.0 / 6.6).  Off the lines one round of 16-row or nearly full 32-row tiles
+//    (4096 x 10000 19.9 / 18.3, 8000 x 11100 38.4 / 34.9; 5120 x 10000 25.1 / 26.9).
+//  * Two tokens, 2048 to 4096: nearly full rounds (4096 x 4096 9.3 / 8.5, 8192 x 4096
+//    15.4 / 13.8; 3072 x 3584 7.2 / 8.1, 5120 x 2560 8.0 / 8.5, off the lines 6144 x 3686
+//    12.0 / 13.4).
 bool use_gemv(int R, int Cc, int D) {
     if (!espace::gemv_supported(R, D)) return false;
-    if (R == 1) return !(D > 4096 && Cc < 8192);
-    return !(Cc <= 16384 && (D > 4096 || (D > 2048 && Cc >= 4096)));
+    const double rows = (double)Cc / device_cus();   // per CU
+    const bool on = off_lines(D) == 0;
+    bool tiles;
+    if (R == 1)
+        tiles = on && D > 4096 &&
+                ((rows >= 6 && rows <= 16 && (D < 6144 || D > 8192)) || (rows >= 20 && rows < 32 && D >= 13824));
+    else if (D <= 2048)
+        tiles = false;
+    else if (D <= 4096)
+        tiles = (rows >= 14 && rows <= 16) || (rows >= 28 && rows <= 32) || (on && rows >= 24 && rows < 60);
+    else if (!on)
+        tiles = (rows >= 4 && rows <= 16) || (rows >= 28 && rows <= 32);
+    else
+        tiles = (rows <= 48 && (rows >= 5 || D <= 6144 || D > 8192)) || (rows <= 64 && D > 8192 && D < 16384);
+    return !tiles;
 }
 
 constexpr int kMidMaxTokens = 1024;

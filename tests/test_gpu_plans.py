@@ -22,6 +22,14 @@ CASES = [
     (6457, 640, 4736, "tiled", "128x128", 2, 1),        # 53, 128 x 192 tiles 58
     (4096, 1536, 11008, "tiled", "128x192", 1, 0),      # 130, pairs of 256 x 192 tiles 156
     (12288, 1536, 4096, "tiled", "192x192", 1, 0),      # 142, two launches by rows 149
+    (1, 512, 8192, "gemv", None, 1, 0),                 # 4.6, small tiles 6.6
+    (1, 5120, 8192, "gemv", None, 1, 0),                # 17.8, small tiles 18.8
+    (1, 640, 12231, "gemv", None, 1, 0),                # 8.0, small tiles 10.1
+    (1, 6144, 24576, "small", None, 1, 0),              # 54, in four ranges 60, streamed 58
+    (1, 1536, 11008, "small", None, 1, 0),              # 10.0, streamed 10.7
+    (2, 6144, 3686, "gemv", None, 1, 0),                # 12.0, small tiles 13.4
+    (2, 16384, 8192, "gemv", None, 1, 0),               # 49.9, small tiles 52.2
+    (2, 4096, 11008, "small", None, 1, 0),              # 18.6, streamed 25.4
 ]
 
 
