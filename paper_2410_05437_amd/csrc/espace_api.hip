@@ -283,14 +283,26 @@ int off_lines(int64_t D) {
     return bytes % 128 == 0 ? 0 : (bytes % 64 == 0 ? 1 : 2);
 }
 
-// 3 to 16 tokens on more rows of B than one round of the small-tile kernel's
-// widest tiles holds: the persistent streaming kernel, which balances groups
-// of 16 rows over the CUs (28000 x 1536 at 16 tokens 17.8 against 19.8 µs,
-// 32000 x 4096 48 against 52).  Below that the small tiles are level or
-// faster (22016 x 1536: 14.1 against 15.0, 12288 x 1536: 9.1 against 10.2, 9000
-// x 6144: 22.8 against 27.9).
+// 3 to 16 tokens: the persistent streaming kernel, which balances groups of 16 rows
+// over the CUs and reads 1 KB of a row at a time, where the small tiles (128 bytes of
+// a row at a time) lose to it.
+//  * More rows of B than one round of the widest small tiles holds: 28672 x 1536 at 3
+//    tokens 18.2 against 18.7 us, 28000 x 1536 at 16 tokens 17.8 against 19.8.
+//  * Rows off the cache lines, from 24 rows per CU on (56 at shallow depths): 6144 x
+//    3686 at 8 tokens 12%, 14336 x 5000 at 16 13%, 24576 x 1000 at 3 9% faster; 4096 rows
+//    within 5% either way, 8192 x 1229 2% slower.
+//  * Rows on half lines, up to 8 tokens from 40 rows per CU on: 24576 x 2458 at 3
+//    tokens 24.0 against 25.9 us, at 8 24.4 against 25.2, 11008 x 2458 at 8 12.9 against
+//    13.3; 16384 x 5024 level, 14336 x 2080 5% slower.
+// Otherwise the small tiles are level to 20% faster (22016 x 1536 at 8 tokens 15.1
+// against 15.2 us, 24576 x 4096 at 16 36.1 against 39.5; 16384 x 1536 at 3 the other way,
+// 12.4 against 11.8).
 bool use_stream(int R, int Cc, int D) {
-    return R >= 3 && espace::stream_supported(R, D) && (int64_t)Cc > 96 * (int64_t)device_cus();
+    if (R < 3 || !espace::stream_supported(R, D)) return false;
+    const int64_t cus = device_cus();
+    const int off = off_lines(D);
+    return Cc > 96 * cus || (off == 2 && Cc >= (D > 1800 ? 24 : 56) * cus) ||
+           (off == 1 && R <= 8 && D > 1152 && Cc > 40 * cus);
 }
 
 // One or two tokens: whole-row streaming with bf16 dot products (rows of up to 2048

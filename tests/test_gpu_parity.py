@@ -15,7 +15,7 @@ import torch
 import oracle
 import synth
 from tests import parity
-from tests.gpu_util import dev_mat, host64, need_gpu, out_mat, padding
+from tests.gpu_util import dev_mat, host64, need_gpu, out_mat, padding, plans
 
 pytestmark = pytest.mark.gpu
 
@@ -68,17 +68,13 @@ DEGENERATE = [
 ]
 
 
-# bfloat16 decode plans at N <= 8 (the sizes of the Llama2-7B projection and
-# beyond): whole-row streaming for one and two tokens (tokens in LDS: depth
-# 4500, nine 512-element passes, a full block of eight and a partial one, and
-# depth 3000, six passes with a partial last; tokens in registers: depths
-# 1003, 1536, 131 and 136), two depth segments per MFMA operand with 16 waves (the
-# projection at 8 tokens, 9 row groups over 141 steps) and with 8 waves (its
-# expansion, 57 row groups over 5 steps); one depth range of 132 steps for 132
-# row groups (3 and 5 tokens); two depth segments with two token groups of
-# eight (9 to 16 tokens: 12 tokens on the 141-step projection with 16 waves,
-# 16 tokens on a 125-step projection and its 10-step expansion with 8 waves,
-# 9 tokens, the second group holding one, over 32 and 5 steps).
+# bfloat16 decode plans: whole-row streaming for one and two tokens (tokens in
+# LDS: depth 4500, nine 512-element passes, a full block of eight and a partial
+# one, and depth 3000, six passes with a partial last; tokens in registers:
+# depths 1003, 1536, 131 and 136); small tiles with half-filled operands (8 x 8
+# and 16 x 8, up to 16 tokens on few rows) from 5 to 141 steps deep, and 16 x
+# 16 and 16 x 32 tiles (3 and 5 tokens on 2100 and 4200 rows; 3 tokens on 4100,
+# 8 on 4096 rows, 16 on 8200 rows at 11 steps, 5 on 5000, 16 on 22016).
 DECODE_PLANS = [
     (4500, 900, 136, 8),
     (4500, 900, 136, 12),
@@ -90,6 +86,11 @@ DECODE_PLANS = [
     (4500, 2100, 4200, 5),
     (1003, 517, 131, 2),
     (3000, 700, 136, 1),
+    (1600, 4100, 1537, 3),
+    (6144, 4096, 131, 8),
+    (700, 8200, 700, 16),
+    (1000, 5000, 700, 5),
+    (2000, 22016, 1536, 16),
 ]
 
 
@@ -104,25 +105,27 @@ def test_decode_plans(E, shape):
     _check_entry_points(E, "bf16", shape, seed=45)
 
 
-# 3 to 16 tokens on weights of at least 16 rows per CU (the persistent
-# streaming kernel on the expansion and the dense product): a ragged last
-# group of 16 rows (4100, 8200), workgroups taking two or more groups (8200
-# rows), depths whose last 512-element piece holds 1, 131 and 188 elements
-# (the piece straddling the depth masked in registers) and the deepest
-# supported depth (6144, twelve pieces); workgroups with one group more than
-# others (5000 and 22016 rows: 313 and 1376 groups over the CUs).
+# 3 to 16 tokens on weights whose rows lie off the cache lines (the persistent
+# streaming kernel on the expansion and the dense product): a ragged last group
+# of 16 rows (6200, 6500, 8200, 12300), workgroups with one group more than
+# others (6200 rows: 388 groups over the CUs) or three or four (12300), depths
+# whose last 512-element piece holds 1, 131 and 180 elements (the piece
+# straddling the depth masked in registers) and twelve pieces (6130).
 STREAM_PLANS = [
-    (1600, 4100, 1537, 3),
-    (6144, 4096, 131, 8),
-    (700, 8200, 700, 16),
-    (1000, 5000, 700, 5),
-    (2000, 22016, 1536, 16),
+    (2049, 6200, 1812, 3),
+    (6130, 6160, 2179, 8),
+    (2228, 8200, 2179, 16),
+    (2700, 6500, 1966, 5),
+    (2049, 12300, 1900, 16),
 ]
 
 
 @pytest.mark.parametrize("shape", STREAM_PLANS, ids=lambda s: "K%d_M%d_L%d_N%d" % s)
-def test_stream_plans(E, shape):
-    _check_entry_points(E, "bf16", shape, seed=47)
+def test_stream_plans(E, capfd, shape):
+    K, M, L, N = shape
+    _, ps = plans(capfd, lambda: _check_entry_points(E, "bf16", shape, seed=47))
+    depths = sorted(p["D"] for p in ps if p["kind"] == "stream" and p["R"] == N and p["Cc"] == M)
+    assert depths == [L, L, K]                # the layer's expansion, the expansion, the dense product
 
 
 def _check_entry_points(E, dtype, shape, seed=0):
@@ -681,14 +684,14 @@ def test_decode_layer_shapes(E, shape):
         assert torch.equal(E.espace_projected_linear(X, Pt, Wf, workspace=ws), Y), fill
 
 
-@pytest.mark.parametrize("N", [1, 16])
-def test_decode_layer_under_graph_replay(E, N):
+@pytest.mark.parametrize("N,L", [(1, 1536), (16, 1536), (16, 1966)])
+def test_decode_layer_under_graph_replay(E, N, L):
     """The decode layer captured in a HIP graph and replayed with new tokens
     copied in between: every replay equals the eager call bitwise (one token:
-    the whole-row kernels; 16 tokens: the depth-segmented projection and the
-    LDS-ring expansion)."""
+    the whole-row kernels; 16 tokens: small tiles, and at L = 1966, rows off the
+    cache lines, the LDS-ring expansion)."""
     dev = need_gpu()
-    K, M, L = 4096, 12288, 1536
+    K, M = 4096, 12288
     inps = [_inputs(K, M, L, N, "bf16", seed=95 + i) for i in range(2)]
     X, Pt, W = _dev_inputs(inps[0], dev)
     Wf = E.espace_fold_weights(W, Pt)

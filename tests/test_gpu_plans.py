@@ -30,6 +30,13 @@ CASES = [
     (2, 6144, 3686, "gemv", None, 1, 0),                # 12.0, small tiles 13.4
     (2, 16384, 8192, "gemv", None, 1, 0),               # 49.9, small tiles 52.2
     (2, 4096, 11008, "small", None, 1, 0),              # 18.6, streamed 25.4
+    (3, 24576, 2458, "stream", None, 1, 0),             # 24.0, small tiles 25.9
+    (8, 6144, 3686, "stream", None, 1, 0),              # 13.1, small tiles 14.9
+    (16, 14336, 5000, "stream", None, 1, 0),            # small tiles 13% more
+    (16, 24576, 1000, "stream", None, 1, 0),            # small tiles 7% more
+    (16, 4096, 4096, "small", None, 1, 0),              # 9.0, streamed 11.1
+    (8, 24600, 6144, "stream", None, 1, 0),             # the deepest it takes
+    (16, 28000, 1536, "stream", None, 1, 0),            # 17.8, small tiles 19.8
 ]
 
 
