@@ -696,7 +696,13 @@ espace_status run_tn(const void* A, int64_t lda, const void* B, int64_t ldb, voi
                 if (p.pair2) g.epoch = next_epoch();
                 e = launch_tiled(g, stream);
             }
-        } else if (p.kind == KIND_MID) {
+        } else if (p.kind == KIND_MID || (p.kind == KIND_STREAM && Cc * ldb * 2 >= ((int64_t)1 << 31))) {
+            if (p.kind == KIND_STREAM) {
+                // B past the streaming kernel's 32-bit offsets: small tiles, which
+                // address B tile by tile, in one depth range (no workspace is planned)
+                espace::mid_plan((int)R, (int)Cc, (int)D, device_cus(), &g.tile, &g.splits);
+                g.splits = 1;
+            }
             if (espace::mid_supported(lda, ldb)) {
                 e = espace::launch_mid_tn_bf16(g, stream);
             } else {

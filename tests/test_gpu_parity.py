@@ -356,11 +356,13 @@ def test_invalid_arguments_write_nothing(E):
     assert (host64(Y) == 7.0).all()
 
 
-def test_matrices_past_2g_elements(E):
+@pytest.mark.parametrize("N", [1, 8, 48])
+def test_matrices_past_2g_elements(E, N):
     """A weight of 524296 x 4096 bf16 (more than 2^31 elements, 4 GiB) takes the
-    kernel with 64-bit row offsets; every output against the oracle."""
+    kernels with 64-bit row offsets (8 tokens: small tiles in place of the streaming
+    kernel); every output against the oracle."""
     dev = need_gpu()
-    M, K, N = (1 << 19) + 8, 4096, 48
+    M, K = (1 << 19) + 8, 4096
     assert M * K >= 1 << 31
     W = torch.empty((M, K), dtype=torch.bfloat16, device=dev)
     kk = torch.arange(K, device=dev, dtype=torch.int32)[None, :]
