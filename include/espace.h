@@ -342,15 +342,17 @@ int espace_abi_version(void);
 
 /* Allocation-free variant of espace_projected_linear, for callers that cannot
  * allocate device memory (code under HIP graph capture, tight serving loops,
- * harnesses that forbid hipMalloc).  Same arguments, computation and results
- * as espace_projected_linear without the workspace: Z and the partial sums
- * live in a static device array of ESPACE_NOALLOC_SCRATCH_BYTES that the
+ * harnesses that forbid hipMalloc).  Same arguments, computation and (but for
+ * the sizes below) bits as espace_projected_linear without the workspace: Z and
+ * the partial sums live in a static device array of ESPACE_NOALLOC_SCRATCH_BYTES that the
  * library holds on every device it runs on until the process ends.  Calls
  * neither hipMalloc, hipFree nor any allocating library routine (the first
  * call on a device looks up that device's copy of the array).
- *  - Sizes whose workspace (espace_workspace_bytes(ESPACE_OP_PROJECTED_LINEAR,
- *    ...)) exceeds ESPACE_NOALLOC_SCRATCH_BYTES return ESPACE_ERR_WORKSPACE
- *    and enqueue nothing.
+ *  - Where the array holds Z but not the partial sums besides it (the sizes
+ *    whose espace_workspace_bytes(ESPACE_OP_PROJECTED_LINEAR, ...) exceeds it),
+ *    the products run without a depth split: sums in another order, and slower.
+ *  - Sizes whose Z alone exceeds ESPACE_NOALLOC_SCRATCH_BYTES return
+ *    ESPACE_ERR_WORKSPACE and enqueue nothing.
  *  - All calls on one device share the array: calls that can overlap on one
  *    device (other streams, other threads, other processes are not affected)
  *    race and must be serialised by the caller.  Nothing in it needs to start

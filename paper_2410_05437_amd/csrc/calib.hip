@@ -396,7 +396,7 @@ AutocorrPlan autocorr_plan(int64_t M, int64_t K, int cus) {
     // 512, 16384 tokens 106 -> 34, of which the accumulation's share is 60)
     if (K <= 2048) {
         int config = 0, s = 1;
-        const double us = mid_plan((int)K, (int)K, (int)M, cus, &config, &s);
+        const double us = mid_plan((int)K, (int)K, (int)M, cus, 4, &config, &s);
         if (s <= most && us < best_us) best = AutocorrPlan{config, 0, s};
     }
     return best;

@@ -174,7 +174,8 @@ void set_partial_bytes(Plan& p, int64_t R, int64_t Cc) {
 constexpr double kUnitUs = 24.85e-6;
 struct TileShape { int tile, bm, bn, per_cu; double rate, off_line, round; };
 
-Plan plan_tiled_one(int R, int Cc, int D, int cus, double* cost_out) {
+// ranges: the most depth ranges; 1 leaves no partial sums and no pairs
+Plan plan_tiled_one(int R, int Cc, int D, int cus, int ranges, double* cost_out) {
     // Estimated time of each tile shape (and depth split) from the number of
     // rounds of workgroups the chip needs; the cheapest wins.  Two depth halves
     // can also be combined inside the kernel ("pair"), which costs one fp32 tile
@@ -204,7 +205,7 @@ Plan plan_tiled_one(int R, int Cc, int D, int cus, double* cost_out) {
     for (const TileShape& s : shapes) {
         const int64_t tiles = (int64_t)ceil_div(R, s.bm) * ceil_div(Cc, s.bn);
         const int64_t slots = (int64_t)cus * s.per_cu;
-        for (int splits = 1; splits <= 4; ++splits) {
+        for (int splits = 1; splits <= ranges; ++splits) {
             if (splits > 1 && ktiles / splits < 8) break;
             const bool halving = s.tile == espace::TILE_192x192 || s.tile == espace::TILE_256x160;
             for (int pair = 0; pair <= (splits == 2 && !halving ? 1 : 0); ++pair) {
@@ -240,7 +241,7 @@ Plan plan_tiled_one(int R, int Cc, int D, int cus, double* cost_out) {
     return best;
 }
 
-Plan plan_tiled(int R, int Cc, int D, int cus, double* cost_out) {
+Plan plan_tiled(int R, int Cc, int D, int cus, int ranges, double* cost_out) {
     // A product whose tiles leave the last round of workgroups partly empty
     // can run as two launches split by rows, each with whole rounds.  Taken
     // when the model prices it at least 3% cheaper, a launch counted as 2.7 µs
@@ -252,15 +253,15 @@ Plan plan_tiled(int R, int Cc, int D, int cus, double* cost_out) {
     // ranges and the rest in two rounds.  The QKV fold, 12288 x 1536 x 4096, fits two
     // rounds of 192 x 192 tiles: 142 µs against 149 split by rows.
     double cost = 0;
-    Plan best = plan_tiled_one(R, Cc, D, cus, &cost);
+    Plan best = plan_tiled_one(R, Cc, D, cus, ranges, &cost);
     *cost_out = cost;
     if (R > 32768) return best;   // many rounds: the last one's share is small
     constexpr double kLaunch = 110e3;
     double best_split = 0.97 * cost;
     for (int r1 = 256; r1 < R; r1 += 256) {
         double c1 = 0, c2 = 0;
-        const Plan p1 = plan_tiled_one(r1, Cc, D, cus, &c1);
-        const Plan p2 = plan_tiled_one(R - r1, Cc, D, cus, &c2);
+        const Plan p1 = plan_tiled_one(r1, Cc, D, cus, ranges, &c1);
+        const Plan p2 = plan_tiled_one(R - r1, Cc, D, cus, ranges, &c2);
         if (c1 + c2 + kLaunch < best_split) {
             best_split = c1 + c2 + kLaunch;
             *cost_out = best_split;
@@ -346,15 +347,15 @@ bool use_gemv(int R, int Cc, int D) {
 
 constexpr int kMidMaxTokens = 1024;
 
-Plan plan_mid(int R, int Cc, int D, int cus, double* us) {
+Plan plan_mid(int R, int Cc, int D, int cus, int ranges, double* us) {
     Plan p;
     p.kind = KIND_MID;
-    *us = espace::mid_plan(R, Cc, D, cus, &p.tile, &p.splits);
+    *us = espace::mid_plan(R, Cc, D, cus, ranges, &p.tile, &p.splits);
     if (p.splits > 1) p.partial_bytes = (size_t)p.splits * R * espace::splitk_ld(Cc) * sizeof(float);
     return p;
 }
 
-Plan plan_bf16(int R, int Cc, int D) {
+Plan plan_bf16(int R, int Cc, int D, int ranges) {
     const int cus = device_cus();
     double us = 0;
     if (R <= 32) {
@@ -367,14 +368,14 @@ Plan plan_bf16(int R, int Cc, int D) {
             g.kind = KIND_STREAM;
             return g;
         }
-        return plan_mid(R, Cc, D, cus, &us);
+        return plan_mid(R, Cc, D, cus, ranges, &us);
     }
     double cost = 0;
-    const Plan t = plan_tiled(R, Cc, D, cus, &cost);
+    const Plan t = plan_tiled(R, Cc, D, cus, ranges, &cost);
     if (R > kMidMaxTokens) return t;
     // the tiled plan's price in µs: its units, a launch and its ramp
     const double tiled_us = 4.75 + kUnitUs * cost;
-    const Plan m = plan_mid(R, Cc, D, cus, &us);
+    const Plan m = plan_mid(R, Cc, D, cus, ranges, &us);
     // from 33 tokens on the small tiles' price is 5% high on average, at shallow
     // depths 6% low (64 x 24576 x 1966: 28.0 against 34.1 us, both priced 30.7; 282 x 7701
     // x 384: 12.2 against 9.0)
@@ -384,32 +385,36 @@ Plan plan_bf16(int R, int Cc, int D) {
 // A product's plan depends on its sizes and the device's CUs alone; each
 // thread keeps the last ones it made (a call asks for the same few plans
 // several times: workspace size, layout of Z, launches).
-Plan plan_tn(int64_t R, int64_t Cc, int64_t D, espace_dtype dt) {
+// ranges = 1: the plan without workspace, for a call whose scratch is too small for
+// the faster one's partial sums.
+constexpr int kMaxRanges = 4;
+Plan plan_tn(int64_t R, int64_t Cc, int64_t D, espace_dtype dt, int ranges = kMaxRanges) {
     if (dt == ESPACE_F32) return Plan{};
-    struct Entry { int R = 0, Cc = 0, D = 0, cus = 0; Plan p; };
+    struct Entry { int R = 0, Cc = 0, D = 0, cus = 0, ranges = 0; Plan p; };
     struct Set { Entry e[4]; unsigned next = 0; };
     static thread_local Set memo[16];
     const int cus = device_cus();
     const unsigned h = ((unsigned)R * 2654435761u) ^ ((unsigned)Cc * 2246822519u) ^ ((unsigned)D * 3266489917u);
     Set& set = memo[(h >> 20) % 16];
     for (const Entry& e : set.e)
-        if (e.R == R && e.Cc == Cc && e.D == D && e.cus == cus) return e.p;
+        if (e.R == R && e.Cc == Cc && e.D == D && e.cus == cus && e.ranges == ranges) return e.p;
     Entry& e = set.e[set.next++ % 4];
-    e.p = plan_bf16((int)R, (int)Cc, (int)D);
+    e.p = plan_bf16((int)R, (int)Cc, (int)D, ranges);
     e.R = (int)R;
     e.Cc = (int)Cc;
     e.D = (int)D;
     e.cus = cus;
+    e.ranges = ranges;
     return e.p;
 }
 
 // ESPACE_PLAN_LOG=1 prints each product's plan to stderr (read once per process).
-Plan plan_tn_logged(int64_t R, int64_t Cc, int64_t D, espace_dtype dt) {
+Plan plan_tn_logged(int64_t R, int64_t Cc, int64_t D, espace_dtype dt, int ranges) {
     static const bool log = [] {
         const char* s = std::getenv("ESPACE_PLAN_LOG");
         return s && std::atoi(s) != 0;
     }();
-    const Plan p = plan_tn(R, Cc, D, dt);
+    const Plan p = plan_tn(R, Cc, D, dt, ranges);
     if (log)
         std::fprintf(stderr,
                      "espace plan R=%lld Cc=%lld D=%lld: kind=%d tile=%d splits=%d pair=%d partial=%zu rows1=%d "
@@ -651,13 +656,13 @@ hipError_t launch_tiled(const GemmArgs& g, hipStream_t stream) {
 // only for the tiled plans z_pairs admits
 espace_status run_tn(const void* A, int64_t lda, const void* B, int64_t ldb, void* C, int64_t ldc,
                      int64_t R, int64_t Cc, int64_t D, espace_dtype dt, void* partial,
-                     hipStream_t stream, int a_pairs = 0, int c_pairs = 0) {
+                     hipStream_t stream, int a_pairs = 0, int c_pairs = 0, int ranges = kMaxRanges) {
     hipError_t e;
     if (dt == ESPACE_F32) {
         e = espace::launch_gemm_tn_f32((const float*)A, lda, (const float*)B, ldb, (float*)C, ldc,
                                        (int)R, (int)Cc, (int)D, device_cus(), stream);
     } else {
-        const Plan p = plan_tn_logged(R, Cc, D, dt);
+        const Plan p = plan_tn_logged(R, Cc, D, dt, ranges);
         GemmArgs g;
         g.A = (const uint16_t*)A;
         g.lda = lda;
@@ -700,8 +705,7 @@ espace_status run_tn(const void* A, int64_t lda, const void* B, int64_t ldb, voi
             if (p.kind == KIND_STREAM) {
                 // B past the streaming kernel's 32-bit offsets: small tiles, which
                 // address B tile by tile, in one depth range (no workspace is planned)
-                espace::mid_plan((int)R, (int)Cc, (int)D, device_cus(), &g.tile, &g.splits);
-                g.splits = 1;
+                espace::mid_plan((int)R, (int)Cc, (int)D, device_cus(), 1, &g.tile, &g.splits);
             }
             if (espace::mid_supported(lda, ldb)) {
                 e = espace::launch_mid_tn_bf16(g, stream);
@@ -735,10 +739,10 @@ espace_status run_tn(const void* A, int64_t lda, const void* B, int64_t ldb, voi
 // reduction pass) and every launch of the expand GEMM is a single-range launch of the
 // four-wave kernel.
 bool z_pairs(int64_t N, int64_t L, int64_t K, int64_t M, int64_t ldx, int64_t ldp, int64_t ldwf, int64_t ldy,
-             espace_dtype dt) {
+             espace_dtype dt, int ranges) {
     if (dt != ESPACE_BF16 || N <= 32) return false;
-    const Plan a = plan_tn(N, L, K, dt);
-    const Plan b = plan_tn(N, M, L, dt);
+    const Plan a = plan_tn(N, L, K, dt, ranges);
+    const Plan b = plan_tn(N, M, L, dt, ranges);
     auto v3_single = [](int tile, int splits) {
         return splits == 1 && (tile == espace::TILE_256x256_W8T || tile == espace::TILE_256x192_W8);
     };
@@ -755,18 +759,19 @@ bool z_pairs(int64_t N, int64_t L, int64_t K, int64_t M, int64_t ldx, int64_t ld
 // `workspace` (ws_bytes(ESPACE_OP_PROJECTED_LINEAR, ...) bytes).
 espace_status projected_linear_launch(const void* X, int64_t ldx, const void* Pt, int64_t ldp, const void* Wf,
                                       int64_t ldwf, void* Y, int64_t ldy, int64_t M, int64_t K, int64_t L,
-                                      int64_t N, espace_dtype dt, void* workspace, hipStream_t stream) {
+                                      int64_t N, espace_dtype dt, void* workspace, hipStream_t stream,
+                                      int ranges = kMaxRanges) {
     void* Z = workspace;
     void* partial = (char*)workspace + z_bytes(N, L, dt);
-    if (z_pairs(N, L, K, M, ldx, ldp, ldwf, ldy, dt)) {
+    if (z_pairs(N, L, K, M, ldx, ldp, ldwf, ldy, dt, ranges)) {
         const int64_t ldzp = 2 * z_ld(L, N, dt);   // elements per row pair
-        ESPACE_TRY(run_tn(X, ldx, Pt, ldp, Z, ldzp, N, L, K, dt, partial, stream, 0, 1));
-        ESPACE_TRY(run_tn(Z, ldzp, Wf, ldwf, Y, ldy, N, M, L, dt, partial, stream, 1, 0));
+        ESPACE_TRY(run_tn(X, ldx, Pt, ldp, Z, ldzp, N, L, K, dt, partial, stream, 0, 1, ranges));
+        ESPACE_TRY(run_tn(Z, ldzp, Wf, ldwf, Y, ldy, N, M, L, dt, partial, stream, 1, 0, ranges));
         return ESPACE_OK;
     }
     const int64_t ldz = z_ld(L, N, dt);
-    ESPACE_TRY(run_tn(X, ldx, Pt, ldp, Z, ldz, N, L, K, dt, partial, stream));
-    ESPACE_TRY(run_tn(Z, ldz, Wf, ldwf, Y, ldy, N, M, L, dt, partial, stream));
+    ESPACE_TRY(run_tn(X, ldx, Pt, ldp, Z, ldz, N, L, K, dt, partial, stream, 0, 0, ranges));
+    ESPACE_TRY(run_tn(Z, ldz, Wf, ldwf, Y, ldy, N, M, L, dt, partial, stream, 0, 0, ranges));
     return ESPACE_OK;
 }
 
@@ -992,7 +997,10 @@ espace_status espace_projected_linear_noalloc(const void* X, int64_t ldx, const 
     ESPACE_TRY(check_mat("Pt", Pt, L, K, ldp, dt));
     ESPACE_TRY(check_mat("Wf", Wf, M, L, ldwf, dt));
     ESPACE_TRY(check_mat("Y", Y, N, M, ldy, dt));
-    const size_t need = ws_bytes(ESPACE_OP_PROJECTED_LINEAR, M, K, L, N, dt);
+    // Z and, where they fit as well, the faster plan's partial sums
+    const int ranges = ws_bytes(ESPACE_OP_PROJECTED_LINEAR, M, K, L, N, dt) > (size_t)ESPACE_NOALLOC_SCRATCH_BYTES
+                           ? 1 : kMaxRanges;
+    const size_t need = z_bytes(N, L, dt);
     if (need > (size_t)ESPACE_NOALLOC_SCRATCH_BYTES)
         return fail(ESPACE_ERR_WORKSPACE,
                     "these sizes need %zu bytes of scratch, above the %zu bytes the allocation-free call holds "
@@ -1004,7 +1012,8 @@ espace_status espace_projected_linear_noalloc(const void* X, int64_t ldx, const 
     ESPACE_TRY(check_device());
     void* ws = nullptr;
     ESPACE_TRY(noalloc_scratch(&ws));
-    ESPACE_TRY(projected_linear_launch(X, ldx, Pt, ldp, Wf, ldwf, Y, ldy, M, K, L, N, dt, ws, stream));
+    ESPACE_TRY(projected_linear_launch(X, ldx, Pt, ldp, Wf, ldwf, Y, ldy, M, K, L, N, dt, ws, stream,
+                                       ranges));
     return ok();
 }
 

@@ -287,7 +287,7 @@ hipError_t launch_cfg_mid(const GemmArgs& g, bool upper, hipStream_t stream) {
 // (the rings drain and refill; one workgroup fits a CU), a depth split the reduction
 // launch and its traffic.  Fitted with the tiled kernels' price (espace_api.hip), to
 // 2800 times of these tiles at 3 to 1024 tokens.
-double mid_plan(int R, int Cc, int D, int cus, int* config, int* splits) {
+double mid_plan(int R, int Cc, int D, int cus, int ranges, int* config, int* splits) {
     double best = 1e300;
     const int steps = (D + MK - 1) / MK;
     const int64_t row_bytes = ((int64_t)D + 7) / 8 * 16;
@@ -299,7 +299,7 @@ double mid_plan(int R, int Cc, int D, int cus, int* config, int* splits) {
         if (bn == 8 && R > bm) continue;
         if (bm >= 16 && bm - 16 >= R) continue;    // a smaller tile holds all tokens
         const int64_t tiles = (int64_t)((R + bm - 1) / bm) * ((Cc + bn - 1) / bn);
-        for (int s = 1; s <= 4; ++s) {
+        for (int s = 1; s <= ranges; ++s) {
             if (s > 1 && steps / s < 32) break;    // at least 4 to 8 steps per wave
             // up to 16 tokens: only where the tiles leave most CUs idle (512 x 24576 at
             // one token 14.2 -> 10.8 us with four ranges, but 6144 x 24576 54 -> 60, at 8

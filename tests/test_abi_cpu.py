@@ -3,6 +3,7 @@ header declares, and rejects invalid arguments before touching any device."""
 import ctypes
 
 import pytest
+import torch
 
 import paper_2410_05437_amd as E
 from paper_2410_05437_amd import _lib
@@ -255,6 +256,20 @@ def test_noalloc_rejects_sizes_beyond_its_scratch():
     assert s in (7, 8)
     assert L.espace_projected_linear_noalloc(NULL, 64, P16b, 64, P16c, 16, ctypes.c_void_p(0x60000000), 32,
                                              32, 64, 16, 8, 1, NULL) == 1
+
+
+@pytest.mark.skipif(torch.cuda.is_available(), reason="a valid call with made-up pointers")
+@pytest.mark.parametrize("M,K,Lc,N", [(9273, 10906, 2765, 8561), (6144, 24576, 2458, 8192), (1079, 11471, 642, 8534),
+                                      (8886, 9336, 2286, 10250), (3625, 9863, 1505, 3352), (15796, 21006, 2198, 2460)])
+def test_noalloc_takes_sizes_whose_z_fits(M, K, Lc, N):
+    """Sizes whose Z fits the scratch are accepted, whatever partial sums the plan with
+    a workspace has (more than the scratch, here)."""
+    need = E.espace_workspace_bytes(E.OP_PROJECTED_LINEAR, M, K, Lc, N, torch.bfloat16)
+    assert need > NOALLOC_MAX and (N + 1) * (Lc + 63) * 2 < NOALLOC_MAX
+    ld = [(c + 7) // 8 * 8 for c in (K, K, Lc, M)]
+    X, P, W, Y = (ctypes.c_void_p(i << 44) for i in range(1, 5))
+    s = L.espace_projected_linear_noalloc(X, ld[0], P, ld[1], W, ld[2], Y, ld[3], M, K, Lc, N, 1, NULL)
+    assert s in (7, 8), L.espace_last_error()
 
 
 # MX-FP8 operands: codes [rows][ldq] (ldq >= round_up(cols, 128), % 16), scales

@@ -9,7 +9,7 @@ import torch
 import oracle
 import synth
 from tests import parity
-from tests.gpu_util import dev_mat, host64, need_gpu, out_mat
+from tests.gpu_util import dev_mat, host64, need_gpu, out_mat, plans
 
 pytestmark = pytest.mark.gpu
 
@@ -46,6 +46,33 @@ def test_noalloc_matches_workspace_call():
         B = parity.layer_bound(Y64, Z64, Wf64, parity.row_norms(inp.X), parity.row_norms(inp.Pt),
                                parity.row_norms(inp.W), K, L, parity.U_BF16)
         parity.check(host64(Y_na), Y64, B, parity.TOL["bf16"], f"noalloc K={K} M={M} L={L} N={N}")
+
+
+@pytest.mark.parametrize("M,K,L,N", [(1079, 11471, 642, 8534), (3625, 9863, 1505, 3352)])
+def test_noalloc_without_partial_sums(capfd, M, K, L, N):
+    """Sizes whose partial sums do not fit the scratch beside Z: single depth ranges."""
+    dev = need_gpu()
+    import paper_2410_05437_amd as E
+    assert E.espace_workspace_bytes(E.OP_PROJECTED_LINEAR, M, K, L, N, torch.bfloat16) > 64 << 20
+    g = torch.Generator(device="cuda").manual_seed(N)
+
+    def mat(r, c):
+        t = E.padded_empty(r, c, torch.bfloat16, dev)
+        torch.as_strided(t, (r, t.stride(0)), (t.stride(0), 1)).fill_(float("nan"))
+        return t.copy_(torch.randn(r, c, generator=g, device=dev) * c ** -0.5)
+
+    X, Pt, Wf = mat(N, K), mat(L, K), mat(M, L)
+    Y, ps = plans(capfd, lambda: E.espace_projected_linear_noalloc(X, Pt, Wf, out_mat(N, M, "bf16", dev)))
+    assert len(ps) == 2 and all(p["splits"] == 1 and p["splits2"] == 1 and p["partial"] == 0 for p in ps)
+    Z = (X.double() @ Pt.double().t()).bfloat16().double()
+    ref, mag = Z @ Wf.double().t(), Z.abs() @ Wf.double().abs().t()
+    zmag = X.double().abs() @ Pt.double().abs().t()
+    # Z rounded to bfloat16 (an entry may round the other way after an fp32 sum), then
+    # exact products, fp32 sums of L terms, one rounding
+    dz = 2.0 ** -7 * Z.abs() + (K + 16) * 2.0 ** -23 * zmag
+    bound = 2.0 ** -8 * ref.abs() + 1.01 * (dz @ Wf.double().abs().t()) + 1.01 * (L + 16) * 2.0 ** -23 * mag
+    assert bool(((Y.double() - ref).abs() <= bound).all())
+    assert ((Y.double() - ref).norm() / ref.norm()).item() < 4e-3
 
 
 def test_noalloc_rejects_oversized_call_on_gpu():
