@@ -244,9 +244,38 @@ hipError_t launch_gemm_tn_f32(const float* A, int64_t lda, const float* B, int64
     auto tiles = [&](int t) { return (int64_t)((R + t - 1) / t) * ((Cc + t - 1) / t); };
     // the tiled kernels' 32-bit offsets inside a tile
     const bool fits = (lda > ldb ? lda : ldb) * 128 * 4 < ((int64_t)1 << 32);
-#define LAUNCH(KERNEL, TILE, THREADS)                                                                          \
-    hipLaunchKernelGGL(KERNEL, dim3((unsigned)tiles(TILE)), dim3(THREADS), 0, stream, A, lda, B, ldb, C, ldc, R, \
-                       Cc, D, (Cc + TILE - 1) / TILE)
+    const int few = R < Cc ? R : Cc;
+    auto tiled = [&](auto kernel, int t) {
+        hipLaunchKernelGGL(kernel, dim3((unsigned)tiles(t)), dim3(256), 0, stream, A, lda, B, ldb, C, ldc, R, Cc, D,
+                           (Cc + t - 1) / t);
+        return hipGetLastError();
+    };
+    // one launch unless its 512-thread workgroups were 2^32 threads, a launch's limit
+    auto split = [&](auto kernel, int t) {
+        const int64_t most = 1 << 22;
+        const int64_t tc = (Cc + t - 1) / t < most ? (Cc + t - 1) / t : most;
+        const int64_t cols = tc * t, rows = most / tc * t;
+        for (int64_t r = 0; r < R; r += rows)
+            for (int64_t c = 0; c < Cc; c += cols) {
+                const int nr = (int)(R - r < rows ? R - r : rows), nc = (int)(Cc - c < cols ? Cc - c : cols);
+                hipLaunchKernelGGL(kernel, dim3((unsigned)(((nr + t - 1) / t) * ((nc + t - 1) / t))), dim3(512), 0,
+                                   stream, A + r * lda, lda, B + c * ldb, ldb, C + r * ldc + c, ldc, nr, nc, D,
+                                   (nc + t - 1) / t);
+                const hipError_t e = hipGetLastError();
+                if (e != hipSuccess) return e;
+            }
+        return hipSuccess;
+    };
+    // Few rows or columns first: a tile's unused half or more costs as much as the
+    // used one.  Up to 16 of them, 16 x 16 blocks whose waves split the depth (1 x 32768
+    // x 1024 28 us, 64 x 64 tiles 41, 128 x 128 ones 74; 100000 x 8 x 512 45, 66 and 140); up
+    // to 32, 32 x 32 ones (17 x 65536 x 1024 68, 75 and 135), but at shallow depths 64 x
+    // 64 tiles once they are enough (24 x 65536 x 256 22 against 26, 30000 x 32 x 64 5.8
+    // against 7.0; 32 x 16384 x 256 9.2 against 8.4).
+    if (few <= 16) return split(gemm_tn_f32_split_kernel<16, 8, 4>, 16);
+    const bool shallow = D <= 256 && tiles(64) * 128 >= (int64_t)cus * D;
+    if (few <= 32 && tiles(32) >= 5 * (int64_t)cus / 8 && !(fits && shallow))
+        return split(gemm_tn_f32_split_kernel<32, 8, 4>, 32);
     // 128 x 128 tiles once there is one for every CU (4096^3, 1024 tiles:
     // 1030 against 1079 us with 64 x 64 tiles; 2048 x 2048 x 8192, 256: 542
     // against 549; 1100 x 2048 x 2048, 153: 132 against 103); 64 x 64 tiles
@@ -255,15 +284,11 @@ hipError_t launch_gemm_tn_f32(const float* A, int64_t lda, const float* B, int64
     // that the depth is split over a workgroup's waves: 32 x 32 blocks from
     // 5/8 as many as CUs (200 x 1024 x 1024, 224 blocks: 11 against 17 us
     // with 16 x 16 ones; 200 x 300 x 2000, 70: 16 against 9.5), 16 x 16
-    // blocks below, and always up to 16 rows, where half of a 32-row block
-    // would be empty (16 x 4096 x 2048: 9.7 against 16 us).
-    if (fits && tiles(128) >= cus) LAUNCH((gemm_tn_f32_mfma_kernel<128, 128>), 128, 256);
-    else if (fits && tiles(64) >= cus / 2) LAUNCH((gemm_tn_f32_mfma_kernel<64, 64>), 64, 256);
-    else if (R > 16 && Cc > 16 && tiles(32) >= 5 * (int64_t)cus / 8)
-        LAUNCH((gemm_tn_f32_split_kernel<32, 8, 4>), 32, 512);
-    else LAUNCH((gemm_tn_f32_split_kernel<16, 8, 4>), 16, 512);
-#undef LAUNCH
-    return hipGetLastError();
+    // blocks below.
+    if (fits && few > 64 && tiles(128) >= cus) return tiled(gemm_tn_f32_mfma_kernel<128, 128>, 128);
+    if (fits && tiles(64) >= cus / 2) return tiled(gemm_tn_f32_mfma_kernel<64, 64>, 64);
+    if (tiles(32) >= 5 * (int64_t)cus / 8) return split(gemm_tn_f32_split_kernel<32, 8, 4>, 32);
+    return split(gemm_tn_f32_split_kernel<16, 8, 4>, 16);
 }
 
 }  // namespace espace

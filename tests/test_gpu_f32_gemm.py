@@ -12,7 +12,11 @@ pytestmark = pytest.mark.gpu
 # (tokens, output columns, depth); with 256 CUs: 128 x 128 tiles (272 and 256 of
 # them), 64 x 64 tiles (176, 128), 32 x 32 blocks (175, 160) and 16 x 16 blocks
 SHAPES = [(2049, 1930, 37), (2048, 2048, 64), (700, 1000, 70), (512, 1024, 33), (130, 1100, 100), (160, 1020, 257),
-          (17, 300, 66), (16, 4099, 31), (5000, 7, 40), (1, 1, 1), (1, 2049, 1023), (33, 16, 520)]
+          (17, 300, 66), (16, 4099, 31), (5000, 7, 40), (1, 1, 1), (1, 2049, 1023), (33, 16, 520),
+          # many columns or rows against up to 16 (16 x 16 blocks), up to 32 (32 x 32
+          # blocks; 64 x 64 tiles at shallow depths) and up to 64 of the other
+          (1, 33001, 300), (33001, 7, 300), (17, 9001, 290), (9001, 32, 290), (24, 40003, 130), (40003, 30, 64),
+          (50, 40003, 70), (40003, 64, 70)]
 
 
 def mat(rows, cols, g):
@@ -37,6 +41,17 @@ def test_f32_product(R, C, D):
     bound = (D + 8) * 2.0 ** -24 * (X.double().abs() @ W.double().abs().t())
     assert bool(((Y.double() - ref).abs() <= bound).all())
     assert bool(whole[:, C:].isnan().all())      # nothing written past a row
+
+
+@pytest.mark.parametrize("R,C", [(1, (1 << 26) + 5), ((1 << 26) + 5, 1)])
+def test_f32_more_blocks_than_a_launch(R, C):
+    need_gpu()
+    X = torch.randn(R, 4, device="cuda")
+    W = torch.randn(C, 4, device="cuda")
+    Y = espace.padded_empty(R, C, torch.float32, "cuda", 4).fill_(float("nan"))
+    espace.espace_dense_linear(X, W, Y=Y)
+    ref = X.double() @ W.double().t()
+    assert bool(((Y.double() - ref).abs() <= 12 * 2.0 ** -24 * (X.double().abs() @ W.double().abs().t())).all())
 
 
 @pytest.mark.parametrize("R,C,D", [(700, 1000, 70), (130, 1100, 100), (17, 300, 66)])
