@@ -380,11 +380,16 @@ AutocorrPlan autocorr_plan(int64_t M, int64_t K, int cus) {
     // 36 x 7 ranges of 256 x 256 fit the chip better than 53 x 7 of 256 x 192)
     const int per = (steps + most - 1) / most;
     const int S = (steps + per - 1) / per;                   // no empty range
+    // rows of Xt off the cache lines cost as in the planned products (espace_api.hip;
+    // K = 1860, 1315 tokens: 48 us on small tiles, 57 on these)
+    const int64_t row_bytes = (M + 7) / 8 * 16;
+    const double off_line = row_bytes % 128 == 0 ? 0.0 : (row_bytes % 64 == 0 ? 0.33 : 1.0);
     for (int bn = 256; bn >= 192; bn -= 64) {
         const int64_t items = (int64_t)upper_tiles((int)K, 256, bn) * S;
         const int64_t rounds = (items + cus - 1) / cus;
         const double active = std::min(1.0, (double)items / cus);
-        const double us = 8.0 + rounds * per * (bn == 256 ? 1.0 : 0.78) * std::max(1.1, 1.6 * active) +
+        const double us = 8.0 + rounds * per * (bn == 256 ? 1.0 : 0.78) * std::max(1.1, 1.6 * active) *
+                                    (1.0 + 0.33 * off_line) +
                           4e-6 * S * (double)K * K / 4.0;
         if (us < best_us) {
             best_us = us;
@@ -393,11 +398,17 @@ AutocorrPlan autocorr_plan(int64_t M, int64_t K, int cus) {
     }
     // small matrices: tiles of up to 112 x 96 give every CU work, and their waves
     // split the depth (the whole update: K = 700, 1000 tokens 53 -> 14 us; K =
-    // 512, 16384 tokens 106 -> 34, of which the accumulation's share is 60)
+    // 512, 16384 tokens 106 -> 34, of which the accumulation's share is 60).  In as many
+    // ranges as make a wave's sum no longer than a range's on the large tiles: its
+    // error against float64 grows with its length (K = 1069, 5679 tokens: 1.29e-7 in 18
+    // steps, 1.48e-7 in 23)
     if (K <= 2048) {
         int config = 0, s = 1;
-        const double us = mid_plan((int)K, (int)K, (int)M, cus, 4, &config, &s);
-        if (s <= most && us < best_us) best = AutocorrPlan{config, 0, s};
+        double us = mid_plan((int)K, (int)K, (int)M, cus, 4, &config, &s);
+        const int waves = mid_waves(config);
+        auto chain = [&] { return ((steps + s - 1) / s + waves - 1) / waves; };
+        for (; s < most && chain() > per; ++s) us += 1.0 + 1e-6 * (double)K * K;
+        if (s <= most && chain() <= per && us < best_us) best = AutocorrPlan{config, 0, s};
     }
     return best;
 }

@@ -105,8 +105,10 @@ hipError_t launch_gemm_tn_bf16_v3(const GemmArgs& g, hipStream_t stream);
 // Small-tile product for a few to a few hundred tokens (tile: index of the
 // configuration mid_plan chose; splits > 1 needs `partial`).  mid_plan, for up to
 // `ranges` depth ranges, returns the estimated time in us; mid_supported says
-// whether the leading dimensions fit its 32-bit offsets.
+// whether the leading dimensions fit its 32-bit offsets, mid_waves into how many
+// sums a configuration's waves split a range.
 double mid_plan(int R, int Cc, int D, int cus, int ranges, int* config, int* splits);
+int mid_waves(int config);
 bool mid_supported(int64_t lda, int64_t ldb);
 hipError_t launch_mid_tn_bf16(const GemmArgs& g, hipStream_t stream);
 // Vector-ALU product for 1 <= R <= 2 tokens with whole-row streaming (tile,

@@ -67,9 +67,9 @@ constexpr int MK = 64;                            // depth of a step: 128-byte r
     X(80, 32, 4, 2, 1) X(80, 48, 4, 2, 1) X(80, 64, 4, 2, 1) X(80, 80, 4, 2, 1)                               \
     X(96, 32, 4, 2, 1) X(96, 48, 4, 2, 1) X(96, 64, 4, 2, 1) X(112, 48, 4, 2, 1)
 
-struct MidShape { int bm, bn; };
+struct MidShape { int bm, bn, waves; };
 constexpr MidShape kMid[] = {
-#define X(BM, BN, W, ST, SEG) {BM, BN},
+#define X(BM, BN, W, ST, SEG) {BM, BN, W},
     MID_CONFIGS(X)
 #undef X
 };
@@ -319,6 +319,8 @@ double mid_plan(int R, int Cc, int D, int cus, int ranges, int* config, int* spl
     }
     return best;
 }
+
+int mid_waves(int config) { return kMid[config].waves; }
 
 // The tiles' 32-bit offsets.
 bool mid_supported(int64_t lda, int64_t ldb) {

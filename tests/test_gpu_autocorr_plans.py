@@ -38,3 +38,19 @@ def test_update(K, N, normalize):
     assert bool(((C.double() - ref).abs() <= bound).all())
     assert torch.equal(C, C.t())                     # exactly symmetric
     assert bool(whole[:, K:].isnan().all())
+
+
+@pytest.mark.parametrize("K,N,limit", [(1069, 5679, 1.4e-7), (583, 5988, 1.15e-7), (648, 13694, 1.1e-7)])
+def test_accuracy(K, N, limit):
+    """The error against float64 on normal data grows with the length of a sum: 1.29e-7
+    at K = 1069 in 18 steps of 64 tokens, 1.48e-7 in 23 (limits between the two)."""
+    need_gpu()
+    g = torch.Generator(device="cuda").manual_seed(K)
+    X = espace.padded_empty(N, K, torch.bfloat16, "cuda")
+    X.copy_(torch.randn(N, K, generator=g, device="cuda"))
+    C = espace.padded_empty(K, K, torch.float32, "cuda", 4).zero_()
+    espace.espace_autocorrelation_update(X, C, 1.0)
+    ref = X.double().t() @ X.double()
+    err = ((C.double() - ref).norm() / ref.norm()).item()
+    print(f"K={K} N={N} {err:.3e}")
+    assert err < limit
