@@ -162,8 +162,11 @@ void set_partial_bytes(Plan& p, int64_t R, int64_t Cc) {
 //    with one workgroup instead of two on a CU by more.
 //  * Rows that do not start on cache lines (128 bytes) cost each tile `off_line` of
 //    its time, half lines a third of that: a step's 128 bytes of a row are two lines.
-//  * A pair's second half waits for the first's stores, on 256 x 192 tiles for longest
-//    where all run at once.
+//  * A pair's second half waits for the first's stores: 57e3 and the tile's traffic.
+//    (Pairs of 256 x 192 tiles wait for another 12% where all run at once: 4096 x 1536 x
+//    11008 156 against 130 us on 128 x 192 tiles; 31 of a million sizes would take them,
+//    none 256 x 128 or 128 x 256 tiles, the best of all at 2 of the 548 measured, by 4
+//    and 11%: gone.)
 //  * The operands come from HBM at 5.15 TB/s, all but hidden where they take less.
 // Fitted to 16280 measured times (638 sizes of 3 to 12288 rows, 200 to 24576 columns
 // and 300 to 24576 of depth; every tile, 1 to 4 depth ranges, pairs, and the small
@@ -183,8 +186,6 @@ Plan plan_tiled_one(int R, int Cc, int D, int cus, int ranges, double* cost_out)
     static const TileShape shapes[] = {
         {espace::TILE_256x256_W8T, 256, 256, 1, 1.000, 0.331, 101e3},
         {espace::TILE_256x192_W8, 256, 192, 1, 0.933, 0.355, 101e3},
-        {espace::TILE_256x128, 256, 128, 1, 0.727, 0.205, 101e3},
-        {espace::TILE_128x256, 128, 256, 1, 0.701, 0.233, 101e3},
         {espace::TILE_128x128, 128, 128, 2, 0.800, 0.255, 40e3},
         {espace::TILE_128x192, 128, 192, 1, 0.778, 0.242, 60e3},
         {espace::TILE_192x192, 192, 192, 1, 0.905, 0.203, 217e3},
@@ -207,8 +208,9 @@ Plan plan_tiled_one(int R, int Cc, int D, int cus, int ranges, double* cost_out)
         const int64_t slots = (int64_t)cus * s.per_cu;
         for (int splits = 1; splits <= ranges; ++splits) {
             if (splits > 1 && ktiles / splits < 8) break;
-            const bool halving = s.tile == espace::TILE_192x192 || s.tile == espace::TILE_256x160;
-            for (int pair = 0; pair <= (splits == 2 && !halving ? 1 : 0); ++pair) {
+            const bool pairs = s.tile == espace::TILE_256x256_W8T || s.tile == espace::TILE_128x128 ||
+                               s.tile == espace::TILE_128x192;
+            for (int pair = 0; pair <= (splits == 2 && pairs ? 1 : 0); ++pair) {
                 const int64_t blocks = tiles * splits;
                 const int64_t full = blocks / slots, rest = blocks % slots;
                 const bool deep = s.tile == espace::TILE_128x192 && !pair &&
@@ -222,8 +224,7 @@ Plan plan_tiled_one(int R, int Cc, int D, int cus, int ranges, double* cost_out)
                 if (rest)
                     cost += work * (s.per_cu == 2 && fill < 0.5 ? 0.55 + 0.612 * fill : 0.712 + 0.288 * fill) + t.round;
                 if (pair)
-                    cost += 57e3 + 1.48 * tiles * s.bm * s.bn * 4.0 * byte_cost +
-                            (blocks <= slots && s.tile == espace::TILE_256x192_W8 ? 0.122 * work : 0.0);
+                    cost += 57e3 + 1.48 * tiles * s.bm * s.bn * 4.0 * byte_cost;
                 else if (splits > 1)
                     cost += 97e3 + 1.37 * splits * (double)R * Cc * 4.0 * byte_cost;
                 cost = std::max(cost, hbm) + 0.16 * std::min(cost, hbm);
@@ -409,19 +410,33 @@ Plan plan_tn(int64_t R, int64_t Cc, int64_t D, espace_dtype dt, int ranges = kMa
 }
 
 // ESPACE_PLAN_LOG=1 prints each product's plan to stderr (read once per process).
-Plan plan_tn_logged(int64_t R, int64_t Cc, int64_t D, espace_dtype dt, int ranges) {
+bool plan_log() {
     static const bool log = [] {
         const char* s = std::getenv("ESPACE_PLAN_LOG");
         return s && std::atoi(s) != 0;
     }();
+    return log;
+}
+
+Plan plan_tn_logged(int64_t R, int64_t Cc, int64_t D, espace_dtype dt, int ranges) {
     const Plan p = plan_tn(R, Cc, D, dt, ranges);
-    if (log)
+    if (plan_log())
         std::fprintf(stderr,
                      "espace plan R=%lld Cc=%lld D=%lld: kind=%d tile=%d splits=%d pair=%d partial=%zu rows1=%d "
                      "tile2=%d splits2=%d pair2=%d\n",
                      (long long)R, (long long)Cc, (long long)D, (int)p.kind, p.tile, p.splits, p.pair,
                      p.partial_bytes, p.rows1, p.tile2, p.splits2, p.pair2);
     return p;
+}
+
+// The same for an MX-FP8 product: the small-tile configuration, -1 for a tiled
+// kernel, whose tile it names for the projection.
+void log_mx(const espace::MxGemmArgs& a, int out_mx) {
+    if (!plan_log()) return;
+    double us = 0;
+    std::fprintf(stderr, "espace mx plan R=%d Cc=%d D=%d: out_mx=%d pairs=%d small=%d tile=%d\n", a.R, a.C, a.D, out_mx,
+                 a.t_pairs | a.out_pairs, a.t_pairs ? -1 : espace::mx_small_config(a.R, a.C, a.D, device_cus(), out_mx),
+                 out_mx ? (int)espace::mx_proj_tile(a.R, a.C, a.D, device_cus(), &us) : -1);
 }
 
 // Leading dimension of Z in the workspace.  For decode (N <= 32, bf16) the
@@ -812,6 +827,7 @@ espace_status mx_project_launch(const void* Ptq, int64_t ldpq, const void* Pts, 
     a.W = (const uint8_t*)Ptq; a.ldw = ldpq; a.Ws = (const uint8_t*)Pts; a.ldws = ldps;
     a.out = Zq; a.ldo = ldzq; a.outs = (uint8_t*)Zs; a.ldos = ldzs;
     a.R = (int)N; a.C = (int)L; a.D = (int)K; a.cpad = (int)mx_cols(L);
+    log_mx(a, 1);
     const hipError_t e = espace::launch_gemm_mx(a, 1, device_cus(), stream);
     if (e != hipSuccess) return fail(ESPACE_ERR_HIP, "MX-FP8 projection launch: %s", hipGetErrorString(e));
     return ESPACE_OK;
@@ -826,6 +842,7 @@ espace_status mx_expand_launch(const void* Zq, int64_t ldzq, const void* Zs, int
     a.W = (const uint8_t*)Wfq; a.ldw = ldwq; a.Ws = (const uint8_t*)Wfs; a.ldws = ldws;
     a.out = Y; a.ldo = ldy;
     a.R = (int)N; a.C = (int)M; a.D = (int)L; a.cpad = (int)mx_cols(M);
+    log_mx(a, 0);
     const hipError_t e = espace::launch_gemm_mx(a, 0, device_cus(), stream);
     if (e != hipSuccess) return fail(ESPACE_ERR_HIP, "MX-FP8 expansion launch: %s", hipGetErrorString(e));
     return ESPACE_OK;

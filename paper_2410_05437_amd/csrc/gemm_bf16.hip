@@ -279,8 +279,6 @@ hipError_t launch_gemm_tn_bf16(const GemmArgs& g0, hipStream_t stream) {
         case TILE_256x256:
         case TILE_256x256_W8:
         case TILE_256x256_W8T: return launch_cfg<256, 256, 2, 4>(g, stream);
-        case TILE_256x128: return launch_cfg<256, 128, 2, 2>(g, stream);
-        case TILE_128x256:
         case TILE_128x192: return launch_cfg<128, 256, 2, 2>(g, stream);
         case TILE_192x192:
         case TILE_256x160:

@@ -519,20 +519,17 @@ hipError_t launch_v2(const GemmArgs& g, hipStream_t stream) {
 
 void tile_dims(int tile, int* bm, int* bn) {
     switch (tile) {
-        case TILE_256x128: *bm = 256; *bn = 128; return;
-        case TILE_128x256: *bm = 128; *bn = 256; return;
         case TILE_128x128: *bm = 128; *bn = 128; return;
         case TILE_128x192: *bm = 128; *bn = 192; return;
-        case TILE_256x192_W8: *bm = 256; *bn = 192; return;
         default: *bm = 256; *bn = 256; return;
     }
 }
 
-// The tiles other than the hand-ordered kernel's: depth step 64.  256 x 128,
-// 128 x 256 and 128 x 128: four waves, 32 x 32 x 16 MFMA blocks, two LDS
-// stages.  128 x 192 (long depths: gemm_bf16_v4.hip; measured on the Llama2-7B
-// projection, 4096 x 1536 x 4096, one round of 256 tiles): eight waves as 4 x 2 (32 x 96 each, 16 x 16 x 32 blocks) and
-// three stages — with operands streamed from HBM 67-69 us with four waves and
+// The 128 x 128 and 128 x 192 tiles: depth step 64.  128 x 128: four waves, 32 x
+// 32 x 16 MFMA blocks, two LDS stages.  128 x 192 (long depths:
+// gemm_bf16_v4.hip; measured on the Llama2-7B projection, 4096 x 1536 x 4096,
+// one round of 256 tiles): eight waves as 4 x 2 (32 x 96 each, 16 x 16 x 32
+// blocks) and three stages — with operands streamed from HBM 67-69 us with four waves and
 // two stages, 58-60 with three stages, 57-58 with eight waves; four stages
 // were no faster, four waves with 16 x 16 x 32 blocks slower (75-80 us).
 // Matrices of 2^31 elements or more take the register-staged kernel (64-bit
@@ -548,8 +545,6 @@ hipError_t launch_gemm_tn_bf16_v2(const GemmArgs& g, hipStream_t stream) {
         return launch_gemm_tn_bf16(g, stream);   // runs a pair plan as one depth range
     }
     switch (g.tile) {
-        case TILE_256x128: return launch_v2<256, 128, 2, 2, 64, 2>(g, stream);
-        case TILE_128x256: return launch_v2<128, 256, 2, 2, 64, 2>(g, stream);
         case TILE_128x128: return launch_v2<128, 128, 2, 2, 64, 2>(g, stream);
         case TILE_128x192:
             // the depth-halving kernel from 48 steps per range on

@@ -405,14 +405,16 @@ hipError_t launch_v3(const GemmArgs& g, hipStream_t stream) {
         return hipGetLastError();
     }
     dim3 grid(ntiles, S);
-    if (pair) {
-        // partial: tiles x 256 x BN fp32, then one state word per tile
-        unsigned long long* state =
-            reinterpret_cast<unsigned long long*>(g.partial + (size_t)ntiles * V3_BM * BN);
-        hipLaunchKernelGGL((gemm_tn_bf16_v3_kernel<V3_PAIR, BN>), grid, block, 0, stream, g.A, g.lda, g.B,
-                           g.ldb, g.C, g.ldc, g.R, g.Cc, g.D, tiles_c, ntiles, ktps, (int64_t)0, map,
-                           state, g.partial, g.epoch, g.wait, g.c_pairs);
-        return hipGetLastError();
+    if constexpr (BN == 256) {
+        if (pair) {
+            // partial: tiles x 256 x 256 fp32, then one state word per tile
+            unsigned long long* state =
+                reinterpret_cast<unsigned long long*>(g.partial + (size_t)ntiles * V3_BM * BN);
+            hipLaunchKernelGGL((gemm_tn_bf16_v3_kernel<V3_PAIR, BN>), grid, block, 0, stream, g.A, g.lda, g.B,
+                               g.ldb, g.C, g.ldc, g.R, g.Cc, g.D, tiles_c, ntiles, ktps, (int64_t)0, map,
+                               state, g.partial, g.epoch, g.wait, g.c_pairs);
+            return hipGetLastError();
+        }
     }
     const int64_t ldp = splitk_ld(g.Cc);
     const int64_t split_stride = (int64_t)g.R * ldp;

@@ -9,8 +9,6 @@ namespace espace {
 
 enum TileKind {
     TILE_256x256 = 0,
-    TILE_256x128 = 1,
-    TILE_128x256 = 2,
     TILE_128x128 = 3,
     TILE_256x256_W8 = 4,     // 8 waves as 2 x 4 (128 x 64 each)
     TILE_256x256_W8T = 5,    // 8 waves as 4 x 2 (64 x 128 each)
