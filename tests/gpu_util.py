@@ -56,7 +56,7 @@ def padding(t):
     return base[:, C:].float().cpu().numpy()
 
 
-TILES = {0: "256x256", 1: "256x128", 2: "128x256", 3: "128x128", 4: "256x256", 5: "256x256", 6: "128x192",
+TILES = {0: "256x256", 3: "128x128", 4: "256x256", 5: "256x256", 6: "128x192",
          7: "256x192", 8: "192x192", 9: "256x160"}
 
 
@@ -64,12 +64,17 @@ def plans(capfd, call):
     """(call(), the plans of the bfloat16 products it ran): one dict each, with the
     sizes R, Cc, D, the kind of kernel, the tile's name (tiled) or index (small
     tiles), the depth ranges (splits), whether two are combined inside the kernel
-    (pair), and rows1, tile2, ... of a second launch by rows."""
+    (pair), and rows1, tile2, ... of a second launch by rows; of an MX-FP8 product
+    (out_mx: the projection) the small-tile configuration (small, or -1) and the
+    projection's tile otherwise (0: 256 x 256, 1: 128 x 128, 2: 128 x 192)."""
     capfd.readouterr()
     out = call()
     got = []
-    for line in re.findall(r"^espace plan (.*)$", capfd.readouterr().err, re.M):
-        p = {k: int(v) for k, v in re.findall(r"(\w+)=(\d+)", line)}
+    for mx, line in re.findall(r"^espace (mx )?plan (.*)$", capfd.readouterr().err, re.M):
+        p = {k: int(v) for k, v in re.findall(r"(\w+)=(-?\d+)", line)}
+        if mx:
+            got.append(p)
+            continue
         p["kind"] = {0: "tiled", 1: "small", 3: "gemv", 4: "stream"}[p["kind"]]
         if p["kind"] == "tiled":
             p["tile"], p["tile2"] = TILES[p["tile"]], TILES[p["tile2"]]

@@ -5,7 +5,7 @@ bit the same with scale rows on 16 bytes and not."""
 import pytest
 import torch
 
-from tests.gpu_util import need_gpu
+from tests.gpu_util import need_gpu, plans
 from tests.test_gpu_mxfp8_small_tiles import EPS, decoded, quantized
 
 import paper_2410_05437_amd as espace
@@ -15,7 +15,7 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("R,C,D", [(4096, 1536, 1536), (4001, 1500, 1537), (4090, 1441, 1700), (3970, 1530, 1800),
                                    (2048, 2458, 2500), (8100, 1500, 9000)])
-def test_project(R, C, D):
+def test_project(capfd, R, C, D):
     need_gpu()
     got = []
     for pad16 in (True, False):
@@ -24,7 +24,8 @@ def test_project(R, C, D):
         Z = espace.mx_empty(R, C, "cuda")
         Z.codes.fill_(0x7F)
         Z.scales.fill_(0xFF)
-        espace.espace_project_mxfp8(Pt, X, Z=Z)
+        _, (p,) = plans(capfd, lambda: espace.espace_project_mxfp8(Pt, X, Z=Z))
+        assert p["small"] < 0 and p["tile"] == 2, p
         got.append(Z)
     assert torch.equal(got[0].codes, got[1].codes)
     assert torch.equal(got[0].scales[:, :(C + 127) // 128 * 4], got[1].scales[:, :(C + 127) // 128 * 4])

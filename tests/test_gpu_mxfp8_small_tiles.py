@@ -4,7 +4,7 @@ the smallest leading dimension and padded to 16 bytes."""
 import pytest
 import torch
 
-from tests.gpu_util import need_gpu
+from tests.gpu_util import need_gpu, plans
 
 import paper_2410_05437_amd as espace
 
@@ -79,6 +79,28 @@ def test_project(R, C, D):
     bound = 2.0 ** -3 * ref.abs() + 2.0 ** -16 * amax + ((D + 127) // 128 + 1) * EPS * mag
     assert bool(((decoded(Z) - ref).abs() <= bound).all())
     assert ((decoded(Z) - ref).norm() / ref.norm()).item() < 4e-2
+
+
+# every tile configuration in the kernel's order, and those with MX-FP8 output
+CONFIGS = [(1, 41, 153), (1, 4187, 151), (1, 8477, 150), (1, 12555, 153), (1, 17011, 258), (826, 139, 154), (17, 6227, 155),
+           (17, 8615, 161), (68, 4924, 157), (221, 3298, 170), (848, 202, 165), (33, 6517, 163), (67, 5501, 157),
+           (241, 2063, 150), (194, 3497, 277), (354, 2703, 261), (294, 1628, 155), (306, 2373, 154), (345, 2590, 271),
+           (197, 4897, 390), (150, 5275, 266), (232, 5217, 391), (267, 2706, 242), (265, 4065, 274)]
+MX_CONFIGS = {1: (1, 41, 300), 3: (385, 530, 582), 4: (1013, 267, 301), 6: (523, 135, 326), 8: (821, 387, 414),
+              9: (1015, 663, 710), 11: (722, 266, 303), 13: (810, 518, 543), 15: (960, 1061, 1063), 18: (868, 785, 878),
+              21: (1014, 1026, 1103)}
+
+
+@pytest.mark.parametrize("config", range(len(CONFIGS)))
+def test_every_tile(capfd, config):
+    _, ps = plans(capfd, lambda: test_expand(*CONFIGS[config]))
+    assert len(ps) == 2 and all(p["out_mx"] == 0 and p["small"] == config for p in ps), ps
+
+
+@pytest.mark.parametrize("config", MX_CONFIGS)
+def test_every_tile_project(capfd, config):
+    _, ps = plans(capfd, lambda: test_project(*MX_CONFIGS[config]))
+    assert len(ps) == 2 and all(p["out_mx"] == 1 and p["small"] == config for p in ps), ps
 
 
 @pytest.mark.parametrize("M,K,L,N", [(2200, 1500, 700, 8), (22016, 1024, 640, 201), (24576, 2000, 1000, 512)])

@@ -163,30 +163,32 @@ def _check_entry_points(E, dtype, shape, seed=0):
 
 
 # Products whose tiles would leave the last round of workgroups partly empty
-# run as two launches split by rows: the fold of a 12288-row weight at depths
-# 1560 (ragged steps) and 4096 (the Llama2-7B QKV fold: 4096 rows on 128 x 192
-# tiles, then 8192 rows on 256 x 192 tiles), and a dense product of 6500
-# tokens (a ragged second part).
-ROW_SPLIT = [("fold", (1560, 12288, 1536, 64)), ("fold", (4096, 12288, 1536, 64)),
-             ("dense", (1000, 3000, 64, 6500))]
+# run as two launches split by rows: a dense product of 5509 tokens (a ragged
+# second part), folds whose first rows run in two depth halves combined inside
+# the kernel, or whose second part runs in four depth ranges.
+ROW_SPLIT = [("dense", (455, 3511, 64, 5509), ("128x128", 1, 0), ("256x192", 1, 0)),
+             ("fold", (2173, 9910, 1951, 64), ("128x128", 2, 1), ("256x256", 1, 0)),
+             ("fold", (2616, 9804, 1773, 64), ("256x256", 1, 0), ("128x192", 4, 0))]
 
 
 @pytest.mark.parametrize("case", ROW_SPLIT, ids=lambda c: "%s_K%d_M%d_L%d_N%d" % ((c[0],) + c[1]))
-def test_row_split_launches(E, case):
+def test_row_split_launches(E, capfd, case):
     dev = need_gpu()
-    op, (K, M, L, N) = case
+    op, (K, M, L, N), first, second = case
     inp = _inputs(K, M, L, N, "bf16", seed=61)
     X, Pt, W = _dev_inputs(inp, dev)
     u = parity.UNIT["bf16"]
     if op == "fold":
-        got = E.espace_fold_weights(W, Pt, out_mat(M, L, "bf16", dev))
+        got, (p,) = plans(capfd, lambda: E.espace_fold_weights(W, Pt, out_mat(M, L, "bf16", dev)))
         want = oracle.fold(inp.W, inp.Pt)
         B = parity.product_bound(want, parity.row_norms(inp.W), parity.row_norms(inp.Pt), K, u)
     else:
-        got = E.espace_dense_linear(X, W, out_mat(N, M, "bf16", dev))
+        got, (p,) = plans(capfd, lambda: E.espace_dense_linear(X, W, out_mat(N, M, "bf16", dev)))
         want = oracle.dense(inp.X, inp.W)
         B = parity.product_bound(want, parity.row_norms(inp.X), parity.row_norms(inp.W), K, u)
     torch.cuda.synchronize()
+    assert p["rows1"] > 0 and (p["tile"], p["splits"], p["pair"]) == first, p
+    assert (p["tile2"], p["splits2"], p["pair2"]) == second, p
     parity.check(host64(got), want, B, TOL["bf16"], op)
     assert np.isnan(padding(got)).all()
 
@@ -388,16 +390,24 @@ def test_matrices_past_2g_elements(E, N):
 
 
 # (K, M, L, N) whose projection (N x L, depth K) the tile planner runs as two
-# depth halves combined inside the GEMM kernel: on the 128x192 and 256x128
-# tiles, and on the four-wave 256x192 tile (also the Llama2-7B FFN-down
-# workload's plan), there with ragged rows, a column count that is not a
-# multiple of 8 and a depth tail
-PAIR_SHAPES = [(1100, 600, 700, 1000), (4100, 500, 1100, 2500), (3003, 520, 1300, 2500),
-               (4100, 300, 1536, 3000), (4100, 300, 1100, 4096)]
+# depth halves combined inside the GEMM kernel, and the tile: 128 x 192 and 128 x
+# 128, and the four-wave kernel's 256 x 256, with ragged rows, column counts that
+# are not a multiple of 8 and depth tails
+PAIR_SHAPES = [((1097, 600, 129, 1028), "128x192"), ((4100, 500, 1100, 2500), "128x192"),
+               ((3003, 520, 1300, 2500), "128x128"), ((4194, 300, 399, 10941), "256x256"),
+               ((5131, 300, 397, 10916), "256x256")]
+PAIR_IDS = ["K%d_M%d_L%d_N%d_" % s + t for s, t in PAIR_SHAPES]
 
 
-@pytest.mark.parametrize("shape", PAIR_SHAPES, ids=lambda s: "K%d_M%d_L%d_N%d" % s)
-def test_pair_combined_depth_halves(E, shape):
+def _pair_project(E, capfd, tile, *args, **kw):
+    """espace_project, checked to run as combined halves on that tile in one launch."""
+    Z, (p,) = plans(capfd, lambda: E.espace_project(*args, **kw))
+    assert (p["kind"], p["tile"], p["splits"], p["pair"], p["rows1"]) == ("tiled", tile, 2, 1, 0), p
+    return Z
+
+
+@pytest.mark.parametrize("shape,tile", PAIR_SHAPES, ids=PAIR_IDS)
+def test_pair_combined_depth_halves(E, capfd, shape, tile):
     """Projection with the in-kernel pair combine against the oracle; the
     combine is order-independent, so repeated calls are bitwise identical
     whatever the workspace held before (its state words are tagged per call)."""
@@ -405,7 +415,7 @@ def test_pair_combined_depth_halves(E, shape):
     K, M, L, N = shape
     inp = _inputs(K, M, L, N, "bf16", seed=50)
     X, Pt, W = _dev_inputs(inp, dev)
-    Z = E.espace_project(Pt, X, out_mat(N, L, "bf16", dev))
+    Z = _pair_project(E, capfd, tile, Pt, X, out_mat(N, L, "bf16", dev))
     torch.cuda.synchronize()
     Z64 = oracle.project(inp.Pt, inp.X)
     B = parity.product_bound(Z64, parity.row_norms(inp.X), parity.row_norms(inp.Pt), K, parity.U_BF16)
@@ -439,8 +449,8 @@ def _tiles_ok_or_nan(got, ref, bm, bn):
     return nan_tiles
 
 
-@pytest.mark.parametrize("shape", [PAIR_SHAPES[0], PAIR_SHAPES[3]], ids=lambda s: "K%d_M%d_L%d_N%d" % s)
-def test_pair_wait_that_gives_up_writes_nan(E, shape):
+@pytest.mark.parametrize("shape,tile", PAIR_SHAPES[1:4], ids=PAIR_IDS[1:4])
+def test_pair_wait_that_gives_up_writes_nan(E, capfd, shape, tile):
     """The failure path of the bounded wait in the pair combine, forced from
     the host with a wait limit of one poll: a tile whose second half finds
     the first half's sums not yet stored gives up at once, writes NaN over the
@@ -450,7 +460,7 @@ def test_pair_wait_that_gives_up_writes_nan(E, shape):
     K, M, L, N = shape
     inp = _inputs(K, M, L, N, "bf16", seed=55)
     X, Pt, _ = _dev_inputs(inp, dev)
-    ref = host64(E.espace_project(Pt, X))
+    ref = host64(_pair_project(E, capfd, tile, Pt, X))
     torch.cuda.synchronize()
     n0 = E.espace_wait_timeouts()
     nan_tiles = 0
@@ -459,8 +469,7 @@ def test_pair_wait_that_gives_up_writes_nan(E, shape):
         for _ in range(4):
             got = host64(E.espace_project(Pt, X, out_mat(N, L, "bf16", dev)))
             torch.cuda.synchronize()
-            # the pair plans of these shapes use 128 x 192 and 256 x 192 tiles:
-            # compare on 128 x 64 pieces, which both tile sizes cover whole
+            # compare on 128 x 64 pieces, which every tile size covers whole
             nan_tiles += _tiles_ok_or_nan(got, ref, 128, 64)
     finally:
         E.espace_set_wait_limit(0)
@@ -472,8 +481,8 @@ def test_pair_wait_that_gives_up_writes_nan(E, shape):
     assert E.espace_wait_timeouts() == n1
 
 
-@pytest.mark.parametrize("shape", [PAIR_SHAPES[0], PAIR_SHAPES[4]], ids=lambda s: "K%d_M%d_L%d_N%d" % s)
-def test_pair_combine_under_graph_replay(E, shape):
+@pytest.mark.parametrize("shape,tile", PAIR_SHAPES[1:4], ids=PAIR_IDS[1:4])
+def test_pair_combine_under_graph_replay(E, capfd, shape, tile):
     """A captured projection that uses the pair combine replays correctly: each
     replay, with new inputs copied in between and eager work in between,
     matches the eager call bitwise."""
@@ -484,7 +493,7 @@ def test_pair_combine_under_graph_replay(E, shape):
     Z = out_mat(N, L, "bf16", dev)
     ws = torch.empty(E.espace_workspace_bytes(E.OP_PROJECT, 0, K, L, N, torch.bfloat16),
                      dtype=torch.uint8, device=dev)
-    E.espace_project(Pt, X, Z, ws)          # warm-up outside the capture
+    _pair_project(E, capfd, tile, Pt, X, Z, ws)          # warm-up outside the capture
     torch.cuda.synchronize()
     g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g):
@@ -547,10 +556,11 @@ def test_prefill_layer_under_graph_replay(E):
 
 
 # (K, M, L, N) of prefill layers: a projection whose tiles split their depth
-# in two halves combined in-kernel (the Llama2-7B shape class), ragged token
-# blocks, components and features (a feature count that is not a multiple of
-# 8 takes the scalar stores), a projection of more tiles than CUs
-PREFILL_SHAPES = [(4100, 3000, 1536, 4096), (1003, 517, 131, 301), (700, 1234, 520, 5000),
+# in two halves combined in-kernel, one round of 128 x 192 tiles (the Llama2-7B
+# shape class), ragged token blocks, components and features (a feature count
+# that is not a multiple of 8 takes the scalar stores), a projection of more
+# tiles than CUs
+PREFILL_SHAPES = [(4100, 500, 1100, 2500), (4100, 3000, 1536, 4096), (1003, 517, 131, 301), (700, 1234, 520, 5000),
                 (4500, 1000, 4000, 4096), (2048, 4096, 256, 40)]
 
 
@@ -596,12 +606,16 @@ def test_prefill_layer_shapes(E, shape):
 # (K, M, L, N) of prefill layers that keep Z in the row-pair layout (an odd
 # token count, whose last pair has one token; a component count that is not a
 # multiple of 64, or of 8, with the expand GEMM's masked depth tail on row
-# pairs; projections on the 128 x 192 tile, on the four-wave 256 x 192 tile
-# in two depth halves (depth 11008), with a projection depth tail, in two
-# launches split by rows (the first in two depth halves; the GPT3-22B FFN-up
-# class at L = 2458), and in four depth ranges summed by the reduction pass)
-ROW_PAIR_SHAPES = [(4096, 12288, 1536, 4095), (4096, 6000, 1500, 4095), (4100, 12288, 1300, 4095),
-                   (11008, 4096, 1536, 4095), (6144, 2048, 2458, 8191), (8192, 12288, 1000, 2047)]
+# pairs), and the plan of the projection that writes it: tile, depth ranges,
+# pair, first rows of a launch split by rows.
+ROW_PAIR_SHAPES = [((4096, 12288, 1536, 4095), ("128x192", 1, 0, 0)), ((4096, 6000, 1500, 4095), ("128x192", 1, 0, 0)),
+                   ((4100, 12288, 1300, 4095), ("128x192", 1, 0, 0)), ((11008, 4096, 1536, 4095), ("128x192", 1, 0, 0)),
+                   ((6144, 2048, 2458, 8191), ("256x160", 1, 0, 0)), ((8192, 12288, 1000, 2047), ("128x128", 4, 0, 0)),
+                   ((1064, 2980, 132, 2717), ("128x192", 2, 1, 0)), ((1129, 3461, 68, 2351), ("128x128", 2, 1, 0)),
+                   ((5150, 2392, 398, 10997), ("256x256", 2, 1, 0)), ((5867, 1479, 512, 8701), ("256x256", 3, 0, 0)),
+                   ((3301, 942, 380, 10961), ("192x192", 2, 0, 0)), ((3298, 1353, 433, 8771), ("256x160", 2, 0, 0)),
+                   ((2373, 1409, 1952, 10189), ("128x128", 2, 1, 2048)),
+                   ((2041, 6788, 1926, 8719), ("256x256", 1, 0, 8192))]
 
 
 def _row_pairs(Z, ldp):
@@ -616,8 +630,8 @@ def _row_pairs(Z, ldp):
     return out
 
 
-@pytest.mark.parametrize("shape", ROW_PAIR_SHAPES, ids=lambda s: "K%d_M%d_L%d_N%d" % s)
-def test_prefill_layer_row_pair_z(E, shape):
+@pytest.mark.parametrize("shape,plan", ROW_PAIR_SHAPES, ids=["K%d_M%d_L%d_N%d" % s for s, _ in ROW_PAIR_SHAPES])
+def test_prefill_layer_row_pair_z(E, capfd, shape, plan):
     """The prefill layer keeps Z in its workspace in row pairs (two tokens' 32
     consecutive components per 128-byte block): the workspace's Z region holds
     exactly the projection's Z in that layout, the layer's result equals the
@@ -630,7 +644,9 @@ def test_prefill_layer_row_pair_z(E, shape):
     Wf = E.espace_fold_weights(W, Pt)
     need = E.espace_workspace_bytes(E.OP_PROJECTED_LINEAR, M, K, L, N, torch.bfloat16)
     ws = torch.zeros(need, dtype=torch.uint8, device=dev)
-    Y = E.espace_projected_linear(X, Pt, Wf, out_mat(N, M, "bf16", dev), ws)
+    Y, (pp, pe) = plans(capfd, lambda: E.espace_projected_linear(X, Pt, Wf, out_mat(N, M, "bf16", dev), ws))
+    assert (pp["tile"], pp["splits"], pp["pair"], pp["rows1"]) == plan, pp
+    assert pe["tile"] in ("256x256", "256x192") and pe["splits"] == 1, pe
     Z = E.espace_project(Pt, X)
     Ye = E.espace_expand(Z, Wf)
     torch.cuda.synchronize()

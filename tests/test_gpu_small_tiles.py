@@ -4,7 +4,7 @@ projection runs on them while its expansion is tiled."""
 import pytest
 import torch
 
-from tests.gpu_util import need_gpu
+from tests.gpu_util import need_gpu, plans
 
 import paper_2410_05437_amd as espace
 
@@ -45,6 +45,30 @@ def test_small_tiles(C, D):
         espace.espace_dense_linear(X, W, Y=Y)
         check(Y, X, W)
         assert bool(whole[:, C:].isnan().all())      # nothing written past a row
+
+
+# (tokens, rows, depth): every tile configuration in the kernel's order, ragged
+# everywhere, a partial last tile both ways
+CONFIGS = [(3, 41, 157), (9, 42, 161), (17, 41, 159), (3, 4125, 164), (3, 9054, 151), (3, 12347, 150), (3, 17142, 155),
+           (3, 21471, 158), (716, 161, 155), (18, 6497, 155), (17, 10596, 159), (17, 13090, 158), (17, 17597, 166),
+           (17, 21803, 173), (516, 350, 158), (35, 7211, 164), (33, 8911, 166), (33, 13139, 183), (34, 17684, 159),
+           (36, 21335, 151), (763, 325, 153), (957, 527, 151), (98, 5509, 155), (52, 13156, 159), (49, 16599, 167),
+           (162, 7050, 150), (66, 6823, 150), (145, 5303, 153), (69, 12397, 169), (67, 16417, 157), (267, 2706, 196),
+           (954, 1177, 159), (91, 12650, 162), (100, 10651, 154)]
+
+
+@pytest.mark.parametrize("config", range(len(CONFIGS)))
+def test_every_tile(capfd, config):
+    need_gpu()
+    R, C, D = CONFIGS[config]
+    g = torch.Generator(device="cuda").manual_seed(config)
+    X, W = mat(R, D, g), mat(C, D, g)
+    Y = espace.padded_empty(R, C, torch.bfloat16, X.device)
+    whole = torch.as_strided(Y, (R, Y.stride(0)), (Y.stride(0), 1)).fill_(float("nan"))
+    _, (p,) = plans(capfd, lambda: espace.espace_dense_linear(X, W, Y=Y))
+    assert (p["kind"], p["tile"], p["splits"]) == ("small", config, 1), p
+    check(Y, X, W)
+    assert bool(whole[:, C:].isnan().all())
 
 
 @pytest.mark.parametrize("M,K,L,N", [(12288, 4096, 1536, 333), (22016, 4096, 1530, 201), (24576, 1000, 700, 511)])
