@@ -482,7 +482,7 @@ hipError_t launch_autocorr_update(const void* X, int64_t ldx, int M, int K, bool
             g.tile = plan.config;
             e = launch_mid_tn_bf16_ranges(g, stream);
         } else {
-            g.tile = plan.bn == 256 ? TILE_256x256 : TILE_256x192_W8;
+            g.tile = plan.bn == 256 ? TILE_256x256 : TILE_256x192;
             int used = 0;
             e = launch_gemm_tn_bf16_v3_ranges(g, true, &used, stream);
             if (e == hipSuccess && used != S) return hipErrorInvalidValue;

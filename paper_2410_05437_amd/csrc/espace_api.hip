@@ -184,8 +184,8 @@ Plan plan_tiled_one(int R, int Cc, int D, int cus, int ranges, double* cost_out)
     // can also be combined inside the kernel ("pair"), which costs one fp32 tile
     // written and read per output tile instead of a reduction pass.
     static const TileShape shapes[] = {
-        {espace::TILE_256x256_W8T, 256, 256, 1, 1.000, 0.331, 101e3},
-        {espace::TILE_256x192_W8, 256, 192, 1, 0.933, 0.355, 101e3},
+        {espace::TILE_256x256, 256, 256, 1, 1.000, 0.331, 101e3},
+        {espace::TILE_256x192, 256, 192, 1, 0.933, 0.355, 101e3},
         {espace::TILE_128x128, 128, 128, 2, 0.800, 0.255, 40e3},
         {espace::TILE_128x192, 128, 192, 1, 0.778, 0.242, 60e3},
         {espace::TILE_192x192, 192, 192, 1, 0.905, 0.203, 217e3},
@@ -208,7 +208,7 @@ Plan plan_tiled_one(int R, int Cc, int D, int cus, int ranges, double* cost_out)
         const int64_t slots = (int64_t)cus * s.per_cu;
         for (int splits = 1; splits <= ranges; ++splits) {
             if (splits > 1 && ktiles / splits < 8) break;
-            const bool pairs = s.tile == espace::TILE_256x256_W8T || s.tile == espace::TILE_128x128 ||
+            const bool pairs = s.tile == espace::TILE_256x256 || s.tile == espace::TILE_128x128 ||
                                s.tile == espace::TILE_128x192;
             for (int pair = 0; pair <= (splits == 2 && pairs ? 1 : 0); ++pair) {
                 const int64_t blocks = tiles * splits;
@@ -652,7 +652,7 @@ constexpr int64_t kMaxSymDim = 46340;        // K·round_up(K, 8) < 2^31
 
 // One tiled launch of the plan in g.
 hipError_t launch_tiled(const GemmArgs& g, hipStream_t stream) {
-    if (g.tile == espace::TILE_256x256_W8T || g.tile == espace::TILE_256x192_W8) {
+    if (g.tile == espace::TILE_256x256 || g.tile == espace::TILE_256x192) {
         // the four-wave kernel; matrices of 2^31 elements or more take the
         // register-staged kernel with 64-bit offsets (plain layouts only)
         const hipError_t e = espace::launch_gemm_tn_bf16_v3(g, stream);
@@ -759,7 +759,7 @@ bool z_pairs(int64_t N, int64_t L, int64_t K, int64_t M, int64_t ldx, int64_t ld
     const Plan a = plan_tn(N, L, K, dt, ranges);
     const Plan b = plan_tn(N, M, L, dt, ranges);
     auto v3_single = [](int tile, int splits) {
-        return splits == 1 && (tile == espace::TILE_256x256_W8T || tile == espace::TILE_256x192_W8);
+        return splits == 1 && (tile == espace::TILE_256x256 || tile == espace::TILE_256x192);
     };
     if ((a.kind != KIND_TILED && a.kind != KIND_MID) || b.kind != KIND_TILED) return false;
     if (a.kind == KIND_MID && !espace::mid_supported(ldx, ldp)) return false;

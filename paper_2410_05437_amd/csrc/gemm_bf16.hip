@@ -276,13 +276,11 @@ hipError_t launch_gemm_tn_bf16(const GemmArgs& g0, hipStream_t stream) {
         g.pair = 0;
     }
     switch (g.tile) {
-        case TILE_256x256:
-        case TILE_256x256_W8:
-        case TILE_256x256_W8T: return launch_cfg<256, 256, 2, 4>(g, stream);
+        case TILE_256x256: return launch_cfg<256, 256, 2, 4>(g, stream);
         case TILE_128x192: return launch_cfg<128, 256, 2, 2>(g, stream);
         case TILE_192x192:
         case TILE_256x160:
-        case TILE_256x192_W8: return launch_cfg<256, 256, 2, 4>(g, stream);
+        case TILE_256x192: return launch_cfg<256, 256, 2, 4>(g, stream);
         case TILE_128x128: return launch_cfg<128, 128, 2, 2>(g, stream);
         default: return hipErrorInvalidValue;
     }

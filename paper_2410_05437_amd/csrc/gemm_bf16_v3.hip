@@ -451,10 +451,8 @@ hipError_t launch_gemm_tn_bf16_v3_ranges(const GemmArgs& g, bool upper, int* ran
         return hipErrorInvalidValue;
     if (upper && g.R != g.Cc) return hipErrorInvalidValue;
     switch (g.tile) {
-        case TILE_256x256:
-        case TILE_256x256_W8:
-        case TILE_256x256_W8T: return launch_v3_ranges<256>(g, upper, ranges, stream);
-        case TILE_256x192_W8: return launch_v3_ranges<192>(g, upper, ranges, stream);
+        case TILE_256x256: return launch_v3_ranges<256>(g, upper, ranges, stream);
+        case TILE_256x192: return launch_v3_ranges<192>(g, upper, ranges, stream);
         default: return hipErrorInvalidValue;
     }
 }
@@ -474,10 +472,9 @@ hipError_t launch_gemm_tn_bf16_v3(const GemmArgs& g, hipStream_t stream) {
     if ((g.a_pairs && (nranges != 1 || g.lda % 64)) || (g.c_pairs && g.ldc % 64))
         return hipErrorNotSupported;
     switch (g.tile) {
-        case TILE_256x256:
-        case TILE_256x256_W8:
-        case TILE_256x256_W8T: return launch_v3<256>(g, stream);
-        case TILE_256x192_W8: return launch_v3<192>(g, stream);
+        case TILE_256x256: return launch_v3<256>(g, stream);
+        // pairs, whose workspace is sized for them, only on 256 x 256
+        case TILE_256x192: return g.pair ? hipErrorInvalidValue : launch_v3<192>(g, stream);
         default: return hipErrorInvalidValue;
     }
 }

@@ -8,14 +8,12 @@
 namespace espace {
 
 enum TileKind {
-    TILE_256x256 = 0,
-    TILE_128x128 = 3,
-    TILE_256x256_W8 = 4,     // 8 waves as 2 x 4 (128 x 64 each)
-    TILE_256x256_W8T = 5,    // 8 waves as 4 x 2 (64 x 128 each)
-    TILE_128x192 = 6,        // 8 waves as 4 x 2 (32 x 96 each)
-    TILE_256x192_W8 = 7,     // 8 waves as 4 x 2 (64 x 96 each)
-    TILE_192x192 = 8,        // 8 waves as 2 x 2 x 2 depth halves
-    TILE_256x160 = 9,
+    TILE_128x128 = 3,        // gemm_bf16_v2.hip, 4 waves as 2 x 2
+    TILE_256x256 = 5,        // gemm_bf16_v3.hip, 4 waves as 2 x 2 (128 x 128 each)
+    TILE_128x192 = 6,        // gemm_bf16_v2.hip, 8 waves as 4 x 2; long depths as below
+    TILE_256x192 = 7,        // gemm_bf16_v3.hip, 4 waves as 2 x 2 (128 x 96 each)
+    TILE_192x192 = 8,        // gemm_bf16_v4.hip, 8 waves as 2 x 2 x 2 depth halves
+    TILE_256x160 = 9,        // the same
 };
 
 // Limit of the bounded cross-workgroup waits and the device counter of the
