@@ -10,21 +10,24 @@
 // kernel of gemm_bf16_v2.hip); rows are 128 bytes, one request per cache line
 // (the four-wave kernel of gemm_bf16_v3.hip makes two).  One barrier per step.
 // The halves' sums are added through LDS at the end, each wave finishing every
-// other block.  Operands rotated through HBM, us:
+// other block.  Operands rotated through HBM, us, the best of the other
+// kernels -> this one:
 //  * 128 x 192, long depths (one round of 256 tiles on the Llama2-7B
 //    projections): four LDS stages (all 160 KB), one step of fragments read
-//    ahead.  4096 x 1536 x 4096 64 -> 56, x 11008 156 -> 131, x 12288 163 -> 146.
+//    ahead.  4096 x 1536 x 4096 57 -> 56, x 11008 158 -> 134, x 12288 162 -> 145.
 //    Bound by the operands through each CU's load path: the same loads without
 //    arithmetic take 48 of the 55 at depth 4096, the arithmetic alone 40, the
 //    LDS reads alone 22 (10 of each are launch, ramp and writing the tile).
 //    Three stages: 2 more.  Below about 48 steps the sums' exchange costs more
-//    than the loop gains (512 x 12288 x 1536: 27.0 against 25.4).
+//    than the loop gains (512 x 12288 x 1536: 27.0 against 25.2).
 //  * 192 x 192 and 256 x 160, where they fill the chip's rounds better than
 //    256 x 256, 256 x 192 or 128 x 192: too many accumulators for reading
-//    ahead, so the two halves alternate between reading and multiplying.  12288 x
-//    1536 x 4096 153 -> 140 (512 tiles of 192 x 192), 8192 x 2458 x 24576 926 -> 885
-//    (512 of 256 x 160), 333 x 24576 x 2458 61 -> 56.  At equal rounds the
-//    four-wave kernel's larger tiles are 10 to 25% faster.
+//    ahead, so the two halves alternate between reading and multiplying.  512 tiles
+//    of 192 x 192: 12288 x 1536 x 4096 146 (256 x 192) -> 142, in the training step,
+//    its operands partly in the cache, 158 (two launches by rows) -> 152; 512 of 256 x
+//    160: 8192 x 2458 x 24576 982 -> 837 (two launches by rows: 800); 333 x 24576 x 2458
+//    71 -> 57 on 192 x 192.  At equal rounds the four-wave kernel's larger tiles are
+//    10 to 25% faster.
 #include "common.hpp"
 #include "kernels.hpp"
 

@@ -19,18 +19,19 @@
 //    neighbours, so together they read 512 bytes to 1 KB of a row.
 // Rates: 65 to 80 KB/us per CU through the load path, or 4.5 to 5.5 TB/s of B
 // from HBM.  Each XCD starts at another depth (DepthOrder: 333 x 1536 x 11008
-// 33.0 -> 31.0 us, 48 x 12288 x 4096 22.5 -> 20.7).  Measured with operands rotated through HBM against the kernels
-// used before (an MFMA kernel loading straight to registers up to 32 tokens,
-// depth-split 128 x 192 tiles and a reduction pass above), us:
+// 33.0 -> 31.0 us, 48 x 12288 x 4096 22.5 -> 20.7).  Measured as calls of a captured
+// graph, operands rotated through HBM, the gap between two calls included, against
+// the kernels used before (an MFMA kernel loading straight to registers up to 32
+// tokens, depth-split 128 x 192 tiles and a reduction pass above), us:
 //     tokens x rows of B x depth     before   now
-//     13 x  1536 x 11008              20.2   12.7
-//     13 x  2458 x  6144              20.4   10.5
-//     24 x 12288 x  1536              15.1    9.8
-//     48 x  1536 x  4096              19.1    8.4
-//     48 x 12288 x  1536              17.3   11.1
-//     64 x 22016 x  1536              23.8   17.5
-//    128 x  4096 x  1536              17.8    8.7
-//    333 x  2458 x  6144              31.8   24.5
+//     13 x  1536 x 11008              20.7   13.1
+//     13 x  2458 x  6144              20.7   11.0
+//     24 x 12288 x  1536              16.5   11.1
+//     48 x  1536 x  4096              18.9    9.9
+//     48 x 12288 x  1536              17.1   12.5
+//     64 x 22016 x  1536              26.0   20.2
+//    128 x  4096 x  1536              18.2    9.3
+//    333 x  2458 x  6144              31.6   27.7
 //
 // SEG = 2 (up to 16 tokens on few rows of B): the 16 rows of an MFMA operand
 // are 8 rows x the 2 halves of a step, so that twice as many workgroups share

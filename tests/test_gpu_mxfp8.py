@@ -213,8 +213,9 @@ def test_mxfp8_llama2_7b_qkv_sampled(E):
 # the smallest leading dimension (not a multiple of 16 bytes: one scale
 # dword per row and step) and padded to 16 bytes as the library allocates
 # them (four steps' scales per 16-byte load), on 128 x 128 tiles (6 steps: a last group
-# of two; one and several tiles per CU) and 256 x 256 tiles (33 steps).
-SCALE_LAYOUTS = [(5000, 700, 700), (1000, 300, 700), (4096, 4096, 4100)]
+# of two; one and two tiles per CU), small tiles (6 steps) and 256 x 256 tiles (33
+# steps).
+SCALE_LAYOUTS = [(5000, 700, 700), (9000, 700, 700), (1000, 300, 700), (4096, 4096, 4100)]
 
 
 @pytest.mark.parametrize("shape", SCALE_LAYOUTS, ids=lambda s: "N%d_L%d_K%d" % s)
@@ -251,8 +252,8 @@ def test_mxfp8_projection_scale_layouts(E, shape):
 # (N, M, L) of expansions run on both scale layouts: 6 steps over 528 tiles of
 # 256 x 256 (workgroups take two or three tiles, the next tile's first steps
 # loaded ahead, groups of four steps continuing across tiles), 11 steps on
-# the same tiles, and 5 and 25 steps on 256 x 128 tiles.
-EXPAND_LAYOUTS = [(4096, 8448, 700), (4096, 8448, 1400), (2000, 1000, 600), (1000, 3000, 3100)]
+# the same tiles, 5 and 25 steps on 256 x 128 tiles, and 25 steps on small tiles.
+EXPAND_LAYOUTS = [(4096, 8448, 700), (4096, 8448, 1400), (2000, 1000, 600), (2000, 1000, 3100), (1000, 3000, 3100)]
 
 
 @pytest.mark.parametrize("shape", EXPAND_LAYOUTS, ids=lambda s: "N%d_M%d_L%d" % s)
