@@ -29,11 +29,11 @@ import sys
 
 ROOT = os.path.dirname(os.path.abspath(__file__))
 EXPAND_KERNEL = "gemm_tn_bf16_v3_kernel<0, 256, 0>"   # the four-wave 256x256 kernel, bf16 output, plain A
-PROJECT_KERNEL = "gemm_tn_bf16_v2_kernel<128, 192"   # the projection's 128x192 tile
+PROJECT_KERNEL = "gemm_tn_bf16_v4_kernel<128, 192"   # the projection's 128x192 tile
 EXPAND_GRID = 256 * 256                        # one workgroup of 256 threads per CU
 COPY_KERNELS = ("AUnaryFunctor<c10::BFloat16", "MulFunctor")   # torch.mul(bf16, 1.0)
 COPY_BYTES = 1 << 30
-OWN = ("gemm_tn", "skinny_tn", "gemv_", "splitk_reduce", "espace::")
+OWN = ("gemm_tn", "mid_", "gemv_", "stream_tn", "splitk_reduce", "espace::")
 
 
 def _short(name):
@@ -251,7 +251,7 @@ def counters(args):
         mean = {c: sum(v) / len(v) for c, v in ent.items()}
         n = max(len(v) for v in ent.values())
         # a kernel of the layer phase against its own product
-        fl, by = _alg(("project" if "v2_kernel" in k else "expand") if ph == "layer" else ph, probe)
+        fl, by = _alg(("project" if "v4_kernel" in k else "expand") if ph == "layer" else ph, probe)
         busy = f"{mean['MfmaUtil']:.1f}" if "MfmaUtil" in mean else ""
         mo = [mean[c] for c in ("SQ_INSTS_VALU_MFMA_MOPS_BF16", "SQ_INSTS_VALU_MFMA_MOPS_F8") if c in mean]
         mops = f"{sum(mo) * 512 / fl:.3f}" if mo else ""
@@ -282,12 +282,19 @@ def counters(args):
 _PROJ = ("4096 x 1536, depth 4096, 128 x 192 tiles", 32 * 8 * (128 + 192) * 4096 * 2)
 _EXP = ("4096 x 12288, depth 1536, 256 x 256 tiles", 16 * 48 * 512 * 1536 * 2)
 LOADPATH_PHASES = {
-    "project": {"gemm_tn_bf16_v2_kernel<128, 192": _PROJ},
+    "project": {"gemm_tn_bf16_v4_kernel<128, 192": _PROJ},
     "expand": {"gemm_tn_bf16_v3_kernel<0, 256, 0>": _EXP},
     "dense": {"gemm_tn_bf16_v3_kernel<0, 256, 0>": ("4096 x 12288, depth 4096, 256 x 256 tiles",
                                                     16 * 48 * 512 * 4096 * 2)},
-    "layer": {"gemm_tn_bf16_v2_kernel<128, 192": _PROJ,
+    "layer": {"gemm_tn_bf16_v4_kernel<128, 192": _PROJ,
               "gemm_tn_bf16_v3_kernel<0, 256, 1>": ("expand, Z in row pairs: " + _EXP[0], _EXP[1])},
+    "mx_project": {"proj_mx_kernel<128, 192": ("MX-FP8, 4096 x 1536, depth 4096, 128 x 192 tiles",
+                                               32 * 8 * (128 + 192) * 4096)},
+    "mx_expand": {"gemm_mx_kernel<": ("MX-FP8, 4096 x 12288, depth 1536, 256 x 256 tiles", 16 * 48 * 512 * 1536)},
+    # decode (Llama2-7B FFN up+gate): a kernel's token rows are re-read by every workgroup
+    "layer_N8": {"mid_tn_bf16_kernel": ("of 8 x 1536 x 4096, 8 x 22016 x 1536", None)},
+    "layer_N16": {"mid_tn_bf16_kernel": ("of 16 x 1536 x 4096, 16 x 22016 x 1536", None)},
+    "dense_N16": {"mid_tn_bf16_kernel": ("16 x 22016, depth 4096", None)},
 }
 
 
@@ -297,22 +304,22 @@ def loadpath(args):
     channel (16 per XCD, 128); GRBM_GUI_ACTIVE sums the 8 XCDs' active
     cycles, so one unit's share of the kernel's cycles is counter /
     (GRBM_GUI_ACTIVE / 8 x units)."""
-    table = collections.defaultdict(lambda: collections.defaultdict(list))   # (phase, kernel key) -> counters
-    kname = {}
+    table = collections.defaultdict(lambda: collections.defaultdict(list))   # (phase, key, kernel) -> counters
     for path, _ in args.run:
         ds = _dispatches(path)
         for ph, rows in _phases(ds, PROBE_PHASES).items():
             for d in rows:
                 for key in LOADPATH_PHASES.get(ph, {}):
                     if key in d["name"]:
-                        kname[(ph, key)] = _short(d["name"])
                         for c, v in d["c"].items():
-                            table[(ph, key)][c].append(v)
-    lines = ["# Load-path counters of the tiled GEMMs: Llama2-7B fused QKV (K=4096, M=12288, L=1536, N=4096)", "",
+                            table[(ph, key, _short(d["name"]))][c].append(v)
+    lines = ["# Load-path counters of the GEMMs: Llama2-7B fused QKV (K=4096, M=12288, L=1536, N=4096)", "",
              "The projection, the expand GEMM (on a plain Z) and the dense baseline of `bench.py "
              "--kernel-probe`, and the layer's own two kernels (its expand GEMM reads Z in the workspace's "
-             "row-pair layout); bf16, weights rotated over copies larger than the last-level cache.  Counter "
-             "runs (from the repository root, on one MI355X):", "", "```"]
+             "row-pair layout); the MX-FP8 products of the same layer; the small-tile kernel's launches in the "
+             "Llama2-7B FFN up+gate layer (K=4096, M=22016, L=1536) at 8 and 16 tokens and its dense layer at "
+             "16.  bf16 but for the MX-FP8 phases, weights rotated over copies larger than the last-level "
+             "cache.  Counter runs (from the repository root, on one MI355X):", "", "```"]
     lines += [cmd for _, cmd in args.run] + ["```", ""]
     lines += ["Per launch.  Unit shares: counter / (GRBM_GUI_ACTIVE / 8 x units), units = 256 (TA, TD, "
               "TCP: one per CU) or 128 (TCC: one per L2 channel).  TA busy: the address unit; TA stalled: "
@@ -324,27 +331,26 @@ def loadpath(args):
               "| phase | kernel | shape | MFMA busy % | waitcnt % | TA busy % | TA stalled % | TD busy % | "
               "TD stalled % | TCP pending % | L2 busy % | L2 hit % | L2 requests (M) | operand B / request |",
               "|---|---|---|---|---|---|---|---|---|---|---|---|---|---|"]
-    for ph, kernels in LOADPATH_PHASES.items():
-        for key, (shape, opb) in kernels.items():
-            if (ph, key) not in table:
-                continue
-            m = {c: sum(v) / len(v) for c, v in table[(ph, key)].items()}
-            cyc = m.get("GRBM_GUI_ACTIVE", 0.0) / 8.0
+    rows = [(ph, name, *shape) for ph, kernels in LOADPATH_PHASES.items() for key, shape in kernels.items()
+            for name in [t[2] for t in table if t[:2] == (ph, key)]]
+    for ph, name, shape, opb in rows:
+        m = {c: sum(v) / len(v) for t, cs in table.items() if (t[0], t[2]) == (ph, name) for c, v in cs.items()}
+        cyc = m.get("GRBM_GUI_ACTIVE", 0.0) / 8.0
 
-            def share(c, units):
-                return f"{100.0 * m[c] / (cyc * units):.0f}" if c in m and cyc else ""
+        def share(c, units):
+            return f"{100.0 * m[c] / (cyc * units):.0f}" if c in m and cyc else ""
 
-            busy = f"{100.0 * m['SQ_VALU_MFMA_BUSY_CYCLES'] / (cyc * 1024):.0f}" \
-                if "SQ_VALU_MFMA_BUSY_CYCLES" in m and cyc else ""
-            wait = f"{100.0 * m['SQ_WAIT_INST_ANY'] / m['SQ_WAVE_CYCLES']:.0f}" \
-                if "SQ_WAIT_INST_ANY" in m and m.get("SQ_WAVE_CYCLES") else ""
-            req = m.get("TCC_HIT", 0.0) + m.get("TCC_MISS", 0.0)
-            hit = f"{100.0 * m['TCC_HIT'] / req:.0f}" if req else ""
-            lines.append(f"| {ph} | `{kname[(ph, key)]}` | {shape} | {busy} | {wait} | {share('TA_TA_BUSY', 256)} | "
-                         f"{share('TA_ADDR_STALLED_BY_TC_CYCLES', 256)} | {share('TD_TD_BUSY', 256)} | "
-                         f"{share('TD_TC_STALL', 256)} | {share('TCP_PENDING_STALL_CYCLES', 256)} | "
-                         f"{share('TCC_BUSY', 128)} | {hit} | {req / 1e6:.2f} | "
-                         f"{opb / req:.0f} |" if req else "")
+        busy = f"{100.0 * m['SQ_VALU_MFMA_BUSY_CYCLES'] / (cyc * 1024):.0f}" \
+            if "SQ_VALU_MFMA_BUSY_CYCLES" in m and cyc else ""
+        wait = f"{100.0 * m['SQ_WAIT_INST_ANY'] / m['SQ_WAVE_CYCLES']:.0f}" \
+            if "SQ_WAIT_INST_ANY" in m and m.get("SQ_WAVE_CYCLES") else ""
+        req = m.get("TCC_HIT", 0.0) + m.get("TCC_MISS", 0.0)
+        hit = f"{100.0 * m['TCC_HIT'] / req:.0f}" if req else ""
+        per = f"{opb / req:.0f}" if req and opb else ""
+        lines.append(f"| {ph} | `{name}` | {shape} | {busy} | {wait} | {share('TA_TA_BUSY', 256)} | "
+                     f"{share('TA_ADDR_STALLED_BY_TC_CYCLES', 256)} | {share('TD_TD_BUSY', 256)} | "
+                     f"{share('TD_TC_STALL', 256)} | {share('TCP_PENDING_STALL_CYCLES', 256)} | "
+                     f"{share('TCC_BUSY', 128)} | {hit} | {req / 1e6:.2f} | {per} |")
     open(args.out, "w").write("\n".join(lines) + "\n")
     print("\n".join(lines))
 
