@@ -252,7 +252,12 @@ def kernel_probe(E, dev, stream, args, Xr, Pr, Wfr, Ws, Y, ws, Z, wsz, wse, R):
       mx_project, mx_expand    - the MX-FP8 products of the QKV layer
       layer                    - the QKV layer itself (its expand GEMM reads Z
                                  in the workspace's row-pair layout)
-    Every phase rotates its weights over copies larger than the last-level
+      fold, f32                - its fold (12288 x 1536, depth 4096), and the
+                                 fp32 product of two 4096 x 4096 matrices
+      mx_project_N48, mx_expand_N48
+                               - the MX-FP8 projection of the Llama2-7B FFN down
+                                 layer and expansion of the QKV layer at 48 tokens
+    Every phase but f32 rotates its weights over copies larger than the last-level
     cache.  Prints the phase list as JSON."""
     import torch
     bf = torch.bfloat16
@@ -316,6 +321,41 @@ def kernel_probe(E, dev, stream, args, Xr, Pr, Wfr, Ws, Y, ws, Z, wsz, wse, R):
     torch.cuda.synchronize()
     del Xq, Pq, Wq, Zq
     phase("layer", lambda i: E.espace_projected_linear(Xr[i], Pr[i], Wfr[i], Y, ws), R)
+    torch.cuda.synchronize()
+    Rd = copies(Ws.numel() * 2)
+    Wr = [Ws] + [clone_padded(Ws) for _ in range(Rd - 1)]
+    Wf1 = clone_padded(Wfr[0])
+    wsd = torch.empty(max(E.espace_workspace_bytes(E.OP_FOLD, Ws.shape[0], Ws.shape[1], Pr[0].shape[0], 1, bf), 1),
+                      dtype=torch.uint8, device=dev)
+    torch.cuda.synchronize()
+    phase("fold", lambda i: E.espace_fold_weights(Wr[i], Pr[i % R], Wf1, wsd), Rd)
+    torch.cuda.synchronize()
+    del Wr, Wf1, wsd
+    Fa, Fb = (torch.randn(4096, 4096, device=dev) for _ in range(2))
+    Fc = torch.empty(4096, 4096, device=dev)
+    torch.cuda.synchronize()
+    phase("f32", lambda i: E.espace_dense_linear(Fa, Fb, Fc), 1)
+    torch.cuda.synchronize()
+    del Fa, Fb, Fc
+    Xq = E.espace_quantize_mxfp8(_rand_mat(E, 48, 11008, 1.0, dev))
+    Pq = E.espace_quantize_mxfp8(_rand_mat(E, 1536, 11008, 11008 ** -0.5, dev))
+    Wq = E.espace_quantize_mxfp8(Wfr[0])
+    Rp, Rw = copies(Pq.codes.numel()), copies(Wq.codes.numel())
+
+    def mx_copies(q, n):
+        c = [q] + [E.mx_empty(q.rows, q.cols, dev) for _ in range(n - 1)]
+        for m in c[1:]:
+            m.codes.copy_(q.codes)
+            m.scales.copy_(q.scales)
+        return c
+
+    Pq, Wq = mx_copies(Pq, Rp), mx_copies(Wq, Rw)
+    Zq = E.mx_empty(48, 1536, dev)
+    Y48 = E.padded_empty(48, 12288, bf, dev)
+    E.espace_project_mxfp8(Pq[0], Xq, Zq)
+    torch.cuda.synchronize()
+    phase("mx_project_N48", lambda i: E.espace_project_mxfp8(Pq[i], Xq, Zq), Rp)
+    phase("mx_expand_N48", lambda i: E.espace_expand_mxfp8(Zq, Wq[i], Y48), Rw)
     torch.cuda.synchronize()
     print(json.dumps({"kernel_probe": phases, "launches_per_phase": S, "copy_probe_bytes": COPY_PROBE_BYTES,
                       "qkv": {"K": 4096, "M": 12288, "L": 1536, "N": 4096},

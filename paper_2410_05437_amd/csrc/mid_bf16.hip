@@ -18,7 +18,8 @@
 //  * A stage's rows are 128 bytes, whole cache lines; the waves' steps are
 //    neighbours, so together they read 512 bytes to 1 KB of a row.
 // Rates: 65 to 80 KB/us per CU through the load path, or 4.5 to 5.5 TB/s of B
-// from HBM.  Each XCD starts at another depth (DepthOrder: 333 x 1536 x 11008
+// from HBM; short products (8 x 1536 x 4096: data return busy 19% of the time) are
+// launch, ramp and the final sums.  Each XCD starts at another depth (DepthOrder: 333 x 1536 x 11008
 // 33.0 -> 31.0 us, 48 x 12288 x 4096 22.5 -> 20.7).  Measured as calls of a captured
 // graph, operands rotated through HBM, the gap between two calls included, against
 // the kernels used before (an MFMA kernel loading straight to registers up to 32

@@ -14,8 +14,9 @@
 // scale rows do not start on 16 bytes.  The LDS the ring leaves bounds the
 // depth a configuration takes (fits).
 //
-// Bound by the operands through each CU's load path, 70 KB/us, or the weight
-// from HBM.  Measured with operands rotated through HBM, us, against one
+// Priced by the operands through each CU's load path, 70 KB/us, or the weight
+// from HBM; at the sizes below launch, ramp and the final sums weigh as much (48 x
+// 1536 x 11008: data return busy 30% of the time, L2 60%).  Measured with operands rotated through HBM, us, against one
 // 128 x 128 or 256 x 128 tile per workgroup (a few dozen workgroups):
 //     projection   8 x 1536 x  4096   24.1 ->  6.6
 //     projection  48 x 1536 x 11008   71.7 -> 13.2

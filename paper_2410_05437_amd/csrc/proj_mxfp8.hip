@@ -13,8 +13,9 @@
 // Four waves on the same tile, one per SIMD, took 1.0 us a step: a step's loads,
 // its fragment reads (80 KB through LDS) and its 24 MFMAs a wave (0.37 us) came
 // one after the other.  With two waves per SIMD and reads a step ahead they
-// overlap: 0.85 us a step, bound by the 40 KB of operands through each CU's load
-// path (0.6 us a step when nothing else runs).  Operands rotated through HBM, four
+// overlap: 0.85 us a step, 0.6 of it the 40 KB of operands through each CU's load
+// path when nothing else runs.  No unit is saturated (4096 x 1536 x 4096: data return
+// busy 58% of the time, L2 64%, MFMA 25%; the waves wait 42% of theirs).  Operands rotated through HBM, four
 // waves -> this kernel: 4096 x 1536 x 4096 40 -> 35 us, x 11008 90 -> 82 (89 with
 // all XCDs at the same depth), 2048 x 2458 x 6144 52 -> 47.  192 x 192 tiles (no
 // registers left for reading ahead) and 256 x 128 ones in this scheme are slower

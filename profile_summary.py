@@ -121,7 +121,8 @@ def stats(args):
 MARKER = "spin_kernel"           # torch.cuda._sleep, around each of the probe's phases
 # the phases of bench.py --kernel-probe, in launch order
 PROBE_PHASES = ["project", "expand", "dense", "layer_N1", "dense_N1", "layer_N8", "dense_N8",
-                "layer_N16", "dense_N16", "mx_project", "mx_expand", "layer"]
+                "layer_N16", "dense_N16", "mx_project", "mx_expand", "layer", "fold", "f32",
+                "mx_project_N48", "mx_expand_N48"]
 
 
 def _dispatches(path):
@@ -194,6 +195,14 @@ def _alg(phase, probe):
 
     if phase == "mx_project":
         return 2 * q["N"] * q["L"] * q["K"], mx(q["N"], q["K"]) + mx(q["L"], q["K"]) + mx(q["N"], q["L"])
+    if phase == "mx_project_N48":
+        return 2 * 48 * q["L"] * 11008, mx(48, 11008) + mx(q["L"], 11008) + mx(48, q["L"])
+    if phase == "mx_expand_N48":
+        return 2 * 48 * q["M"] * q["L"], mx(48, q["L"]) + mx(q["M"], q["L"]) + 2 * 48 * q["M"]
+    if phase == "fold":
+        return acc.gemm_flops(q["M"], q["L"], q["K"]), acc.gemm_bytes(q["M"], q["L"], q["K"])
+    if phase == "f32":
+        return acc.gemm_flops(4096, 4096, 4096), 2 * acc.gemm_bytes(4096, 4096, 4096)
     if phase == "mx_expand":
         return 2 * q["N"] * q["M"] * q["L"], mx(q["N"], q["L"]) + mx(q["M"], q["L"]) + 2 * q["N"] * q["M"]
     if phase == "project":
@@ -235,13 +244,15 @@ def counters(args):
              "Llama2-7B fused QKV (K=4096, M=12288, L=1536, N=4096): project, expand and dense GEMMs; "
              "Llama2-7B FFN up+gate (K=4096, M=22016, L=1536) at decode token counts N = 1, 8, 16: "
              "every kernel of the layer and of the dense layer; the MX-FP8 products of the QKV layer "
-             "(mx_project, mx_expand).  bf16 (MX-FP8 in the mx phases), weights rotated over copies "
+             "(mx_project, mx_expand); its fold; an fp32 product of 4096 x 4096 matrices (f32); the MX-FP8 "
+             "projection of the FFN down layer (K=11008) and expansion of the QKV layer at 48 tokens.  bf16 "
+             "(MX-FP8 in the mx phases), weights rotated over copies "
              "larger than the last-level cache.", "",
              "Counter runs (from the repository root, on one MI355X), one run per counter set:", "", "```"]
     lines += [cmd for _, cmd in args.run] + ["```", ""]
     lines += ["Columns are means per launch.  MFMA busy: the derived `MfmaUtil` (SQ_VALU_MFMA_BUSY_CYCLES "
               "over GRBM_GUI_ACTIVE times the SIMD count).  MFMA flops: (SQ_INSTS_VALU_MFMA_MOPS_BF16 + "
-              "SQ_INSTS_VALU_MFMA_MOPS_F8) x 512, against the product's 2·R·C·D.  Bytes: FETCH_SIZE and WRITE_SIZE (KiB) scaled by the "
+              "SQ_INSTS_VALU_MFMA_MOPS_F8 + SQ_INSTS_VALU_MFMA_MOPS_F32) x 512, against the product's 2·R·C·D.  Bytes: FETCH_SIZE and WRITE_SIZE (KiB) scaled by the "
               "1 GiB copy of the same run "
               + ", ".join(f"({c} x {v:.4f})" for c, v in sorted(scale.items())) + ".", "",
               "| phase | kernel | grid | launches | MFMA busy % | MFMA flops / algorithmic | "
@@ -253,7 +264,8 @@ def counters(args):
         # a kernel of the layer phase against its own product
         fl, by = _alg(("project" if "v4_kernel" in k else "expand") if ph == "layer" else ph, probe)
         busy = f"{mean['MfmaUtil']:.1f}" if "MfmaUtil" in mean else ""
-        mo = [mean[c] for c in ("SQ_INSTS_VALU_MFMA_MOPS_BF16", "SQ_INSTS_VALU_MFMA_MOPS_F8") if c in mean]
+        mo = [mean[c] for c in ("SQ_INSTS_VALU_MFMA_MOPS_BF16", "SQ_INSTS_VALU_MFMA_MOPS_F8",
+                                   "SQ_INSTS_VALU_MFMA_MOPS_F32") if c in mean]
         mops = f"{sum(mo) * 512 / fl:.3f}" if mo else ""
         fb = mean.get("FETCH_SIZE", 0.0) * 1024 * scale.get("FETCH_SIZE", 0.0)
         wb = mean.get("WRITE_SIZE", 0.0) * 1024 * scale.get("WRITE_SIZE", 0.0)
@@ -292,6 +304,12 @@ LOADPATH_PHASES = {
                                                32 * 8 * (128 + 192) * 4096)},
     "mx_expand": {"gemm_mx_kernel<": ("MX-FP8, 4096 x 12288, depth 1536, 256 x 256 tiles", 16 * 48 * 512 * 1536)},
     # decode (Llama2-7B FFN up+gate): a kernel's token rows are re-read by every workgroup
+    "fold": {"gemm_tn_bf16_v4_kernel<192, 192": ("12288 x 1536, depth 4096, 192 x 192 tiles",
+                                                 64 * 8 * (192 + 192) * 4096 * 2)},
+    "f32": {"gemm_tn_f32_mfma_kernel<128": ("fp32, 4096 x 4096, depth 4096, 128 x 128 tiles",
+                                            32 * 32 * (128 + 128) * 4096 * 4)},
+    "mx_project_N48": {"mid_mx_kernel": ("MX-FP8, 48 x 1536, depth 11008", None)},
+    "mx_expand_N48": {"mid_mx_kernel": ("MX-FP8, 48 x 12288, depth 1536", None)},
     "layer_N8": {"mid_tn_bf16_kernel": ("of 8 x 1536 x 4096, 8 x 22016 x 1536", None)},
     "layer_N16": {"mid_tn_bf16_kernel": ("of 16 x 1536 x 4096, 16 x 22016 x 1536", None)},
     "dense_N16": {"mid_tn_bf16_kernel": ("16 x 22016, depth 4096", None)},
@@ -316,9 +334,10 @@ def loadpath(args):
     lines = ["# Load-path counters of the GEMMs: Llama2-7B fused QKV (K=4096, M=12288, L=1536, N=4096)", "",
              "The projection, the expand GEMM (on a plain Z) and the dense baseline of `bench.py "
              "--kernel-probe`, and the layer's own two kernels (its expand GEMM reads Z in the workspace's "
-             "row-pair layout); the MX-FP8 products of the same layer; the small-tile kernel's launches in the "
+             "row-pair layout); the MX-FP8 products of the same layer and its fold; an fp32 product; MX-FP8 products "
+             "of 48 tokens; the small-tile kernel's launches in the "
              "Llama2-7B FFN up+gate layer (K=4096, M=22016, L=1536) at 8 and 16 tokens and its dense layer at "
-             "16.  bf16 but for the MX-FP8 phases, weights rotated over copies larger than the last-level "
+             "16.  bf16 but where the shape says otherwise, weights rotated over copies larger than the last-level "
              "cache.  Counter runs (from the repository root, on one MI355X):", "", "```"]
     lines += [cmd for _, cmd in args.run] + ["```", ""]
     lines += ["Per launch.  Unit shares: counter / (GRBM_GUI_ACTIVE / 8 x units), units = 256 (TA, TD, "
