@@ -44,6 +44,9 @@
  *    for the same op, shapes and dtype; NULL only when that size is 0.  Its
  *    contents need no initialisation and are undefined after the call.  Calls
  *    that run concurrently must not share a workspace.
+ *  - The same call on the same operands gives the same bits again.  The order of
+ *    a sum depends on the sizes and on where in the output it lies, so equal rows
+ *    of one call, or a row computed among others, may differ in the last bits.
  *  - Every call is asynchronous and stream-ordered on `stream` (NULL = the
  *    default stream).  ESPACE_OK means "validated and enqueued"; faults during
  *    execution surface at the caller's next synchronisation.  Any other status

@@ -33,7 +33,9 @@ __device__ __forceinline__ int mx_scale_byte(float amax) {
 // eighth of the whole groups of four steps further on (groups, so that the
 // steps that share a scale load stay together; a last partial group keeps its
 // place), so that the XCDs read different columns of the operands at a time
-// (measured in proj_mxfp8.hip).
+// (measured in proj_mxfp8.hip).  A row's sums are added in the order of the XCD its
+// tile falls to, so equal rows of one call may differ in the last bits; the same call
+// gives the same bits again.
 struct MxDepthOrder {
     int whole, rot;
     __device__ __forceinline__ explicit MxDepthOrder(int steps) {
